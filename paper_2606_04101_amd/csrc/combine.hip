@@ -16,6 +16,11 @@
 // keep the most row reads in flight: on the DeepSeek-V3-shaped layer this
 // measured 90 us against 99-121 us for persistent waves that walk whole
 // rows, and against 92-105 us for units of 1, 3 or 4 chunks per lane.
+// More than 8 rows per token run in groups of 8, the sums carried in
+// registers from group to group: 3001 tokens of k = 12, H = 4104 (300 MB)
+// take 52.7 us (5.7 TB/s), against 82.8 us (3.6 TB/s) with one row's load in
+// flight at a time.  Groups of 4 or 6 rows, groups of equal size, and 12 or 16
+// rows together measured the same or up to 15 % slower.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -26,9 +31,7 @@ namespace uep {
 constexpr int kCbThreads = 256;
 constexpr int kCbWaves = kCbThreads / kWave;
 constexpr int kCbGrid = 65535;
-constexpr int kCbMaxK = 8;  // rows loaded together per chunk
-constexpr int kCbChunks = 2;       // 16-byte chunks per lane per step
-constexpr int kCbLaneChunks = 2;   // 16-byte chunks per lane per work unit
+constexpr int kCbRows = 8;  // rows loaded together per chunk
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
@@ -76,14 +79,15 @@ __device__ __forceinline__ void token_rows(const int32_t *row_of_slot, const flo
   }
 }
 
-// k <= kCbMaxK.  Work unit: kCbLaneChunks 16-byte chunks per lane of one
-// token's row; the k rows' loads of kCbChunks chunks are in flight together.
+// Work unit: up to kCh 16-byte chunks per lane of one token's row, `per`
+// chunks in all (nblk equal units per row); the loads of up to kCbRows rows
+// are in flight together.  kMany: k > kCbRows, further groups follow.
+template <int kCh, bool kMany>
 __global__ void __launch_bounds__(kCbThreads)
 k_combine(const v4u *__restrict__ y, int64_t n_rows, const float *__restrict__ gate,
-          const int32_t *__restrict__ row_of_slot, int64_t T, int32_t k, int32_t nch,
-          v4u *__restrict__ out, int32_t *status) {
+          const int32_t *__restrict__ row_of_slot, int64_t T, int32_t k, int32_t nch, int32_t nblk,
+          int32_t per, v4u *__restrict__ out, int32_t *status) {
   const int lane = lane_id();
-  const int nblk = (nch + kCbLaneChunks * kWave - 1) / (kCbLaneChunks * kWave);
   const int64_t n_units = T * nblk;
   const int64_t nw = static_cast<int64_t>(gridDim.x) * kCbWaves;
   for (int64_t unit = static_cast<int64_t>(blockIdx.x) * kCbWaves + threadIdx.x / kWave;
@@ -93,75 +97,75 @@ k_combine(const v4u *__restrict__ y, int64_t n_rows, const float *__restrict__ g
     int row;
     float g;
     token_rows(row_of_slot, gate, t, k, lane, n_rows, status, row, g);
-    const int c_end = min(nch, (b + 1) * kCbLaneChunks * kWave);
-    for (int c0 = b * kCbLaneChunks * kWave + lane; c0 < c_end; c0 += kCbChunks * kWave) {
-      v4u v[kCbChunks][kCbMaxK];
+    const int c0 = b * per + lane, c_end = min(nch, (b + 1) * per);
+    float acc[kCh][8] = {};
+    for (int k0 = 0; k0 < (kMany ? k : 1); k0 += kCbRows) {
+      v4u v[kCh][kCbRows];
 #pragma unroll
-      for (int kk = 0; kk < kCbMaxK; ++kk) {
-        const int r = kk < k ? readlane(row, kk) : -1;
+      for (int kk = 0; kk < kCbRows; ++kk) {
+        const int r = k0 + kk < k ? readlane(row, k0 + kk) : -1;
 #pragma unroll
-        for (int u = 0; u < kCbChunks; ++u) {
+        for (int u = 0; u < kCh; ++u) {
           const int cc = c0 + u * kWave;
           if (r >= 0 && cc < c_end)
             v[u][kk] = __builtin_nontemporal_load(y + static_cast<int64_t>(r) * nch + cc);
         }
       }
 #pragma unroll
-      for (int u = 0; u < kCbChunks; ++u) {
+      for (int u = 0; u < kCh; ++u) {
         const int cc = c0 + u * kWave;
-        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kk = 0; kk < kCbMaxK; ++kk) {
-          const int r = kk < k ? readlane(row, kk) : -1;
+        for (int kk = 0; kk < kCbRows; ++kk) {
+          const int r = k0 + kk < k ? readlane(row, k0 + kk) : -1;
           if (r >= 0 && cc < c_end)
-            acc_chunk(acc, __int_as_float(readlane(__float_as_int(g), kk)), v[u][kk]);
+            acc_chunk(acc[u], __int_as_float(readlane(__float_as_int(g), k0 + kk)), v[u][kk]);
         }
-        if (cc < c_end) __builtin_nontemporal_store(pack_chunk(acc), out + t * nch + cc);
+        if (!kMany && cc < c_end)
+          __builtin_nontemporal_store(pack_chunk(acc[u]), out + t * nch + cc);
       }
+    }
+#pragma unroll
+    for (int u = 0; u < kCh; ++u) {
+      const int cc = c0 + u * kWave;
+      if (kMany && cc < c_end)
+        __builtin_nontemporal_store(pack_chunk(acc[u]), out + t * nch + cc);
     }
   }
 }
 
-// any k: one row at a time
-__global__ void __launch_bounds__(kCbThreads)
-k_combine_wide(const v4u *__restrict__ y, int64_t n_rows, const float *__restrict__ gate,
-               const int32_t *__restrict__ row_of_slot, int64_t T, int32_t k, int32_t nch,
-               v4u *__restrict__ out, int32_t *status) {
-  const int lane = lane_id();
-  const int64_t nw = static_cast<int64_t>(gridDim.x) * kCbWaves;
-  for (int64_t t = static_cast<int64_t>(blockIdx.x) * kCbWaves + threadIdx.x / kWave; t < T;
-       t += nw) {
-    int row;
-    float g;
-    token_rows(row_of_slot, gate, t, k, lane, n_rows, status, row, g);
-    for (int cc = lane; cc < nch; cc += kWave) {
-      float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      for (int kk = 0; kk < k; ++kk) {
-        const int r = readlane(row, kk);
-        if (r >= 0)
-          acc_chunk(acc, __int_as_float(readlane(__float_as_int(g), kk)),
-                    y[static_cast<int64_t>(r) * nch + cc]);
-      }
-      out[t * nch + cc] = pack_chunk(acc);
-    }
-  }
+template <int kCh, bool kMany>
+static void start_combine(const v4u *y, int64_t n_rows, const float *gate,
+                          const int32_t *row_of_slot, int64_t T, int32_t k, int32_t nch, v4u *out,
+                          int32_t *status, hipStream_t stream) {
+  // equal units per row, so that a row a little over a multiple of the
+  // unit's width leaves no nearly empty wave
+  const int32_t nblk = (nch + kCh * kWave - 1) / (kCh * kWave);
+  const int32_t per = (nch + nblk - 1) / nblk;
+  const int64_t need = (T * nblk + kCbWaves - 1) / kCbWaves;
+  const dim3 grid(static_cast<unsigned>(need < kCbGrid ? need : kCbGrid));
+  hipLaunchKernelGGL((k_combine<kCh, kMany>), grid, dim3(kCbThreads), 0, stream, y, n_rows, gate,
+                     row_of_slot, T, k, nch, nblk, per, out, status);
 }
 
 hipError_t launch_combine(const uint16_t *y, int64_t n_rows, const float *gate,
                           const int32_t *row_of_slot, int64_t T, int32_t k, int32_t H,
                           uint16_t *out, int32_t *status, hipStream_t stream) {
   const int32_t nch = H / 8;
-  const int64_t units = T * ((nch + kCbLaneChunks * kWave - 1) / (kCbLaneChunks * kWave));
-  const int64_t need = (units + kCbWaves - 1) / kCbWaves;
-  const dim3 grid(static_cast<unsigned>(need < kCbGrid ? need : kCbGrid));
   const v4u *ys = reinterpret_cast<const v4u *>(y);
   v4u *os = reinterpret_cast<v4u *>(out);
-  if (k <= kCbMaxK)
-    hipLaunchKernelGGL(k_combine, grid, dim3(kCbThreads), 0, stream, ys, n_rows, gate,
-                       row_of_slot, T, k, nch, os, status);
+  // k > kCbRows takes the rows in groups of kCbRows.  One chunk per lane where
+  // one-chunk units fill at least 95 % of their lanes, two where they do not
+  // (fewer partly filled waves).  Measured, one / two chunks, T = 3001 rows of
+  // k = 12: H = 7168 85.8 / 89.1 us, 4096 50.0 / 51.2, 5608 70.1 / 71.8; but
+  // 4104 (89 % filled) 55.3 / 52.7, 2880 (94 %) 39.4 / 37.0, and 520 (51 %,
+  // T = 16000) 46.4 / 40.5.
+  const int64_t ones = (nch + kWave - 1) / kWave;
+  if (k <= kCbRows)
+    start_combine<2, false>(ys, n_rows, gate, row_of_slot, T, k, nch, os, status, stream);
+  else if (20 * static_cast<int64_t>(nch) >= 19 * kWave * ones)
+    start_combine<1, true>(ys, n_rows, gate, row_of_slot, T, k, nch, os, status, stream);
   else
-    hipLaunchKernelGGL(k_combine_wide, grid, dim3(kCbThreads), 0, stream, ys, n_rows, gate,
-                       row_of_slot, T, k, nch, os, status);
+    start_combine<2, true>(ys, n_rows, gate, row_of_slot, T, k, nch, os, status, stream);
   return hipGetLastError();
 }
 

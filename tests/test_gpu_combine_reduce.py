@@ -100,6 +100,23 @@ def test_combine_shapes(T, k, H):
     check_combine(y, gate, ros.reshape(T, k))
 
 
+# more rows per token than one group of 8 loads: group remainders, and row
+# widths on both sides of the one- or two-chunk rule (full, 95 %, 94 %, a
+# lane over a wave, one chunk over two waves)
+@pytest.mark.parametrize("k", [9, 16, 17, 64])
+@pytest.mark.parametrize("H", [8, 488, 480, 512, 520, 1032])
+def test_combine_many_rows_per_token(k, H):
+    rng = np.random.default_rng(1000 * k + H)
+    T = 67
+    V = T * k
+    y = bf16_normals(rng, (V, H))
+    gate = softmax_gates(rng, T, k)
+    ros = rng.permutation(V).astype(np.int32)
+    ros[rng.random(V) < 0.15] = -1
+    ros.reshape(T, k)[5] = -1  # a token with no routed slot
+    check_combine(y, gate, ros)
+
+
 def test_combine_special_values():
     """Signed zeros, infinities, NaNs, subnormal rows and subnormal
     products, large values that overflow to infinity, negative gates."""
