@@ -32,6 +32,8 @@ constexpr int kCbThreads = 256;
 constexpr int kCbWaves = kCbThreads / kWave;
 constexpr int kCbGrid = 65535;
 constexpr int kCbRows = 8;  // rows loaded together per chunk
+constexpr int kCbChunks = 2;       // k <= kCbRows: 16-byte chunks per lane per step
+constexpr int kCbLaneChunks = 2;   //               and per lane per work unit
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
@@ -79,14 +81,60 @@ __device__ __forceinline__ void token_rows(const int32_t *row_of_slot, const flo
   }
 }
 
-// Work unit: up to kCh 16-byte chunks per lane of one token's row, `per`
-// chunks in all (nblk equal units per row); the loads of up to kCbRows rows
-// are in flight together.  kMany: k > kCbRows, further groups follow.
-template <int kCh, bool kMany>
+// k <= kCbRows.  Work unit: kCbLaneChunks 16-byte chunks per lane of one
+// token's row; the k rows' loads of kCbChunks chunks are in flight together.
 __global__ void __launch_bounds__(kCbThreads)
 k_combine(const v4u *__restrict__ y, int64_t n_rows, const float *__restrict__ gate,
-          const int32_t *__restrict__ row_of_slot, int64_t T, int32_t k, int32_t nch, int32_t nblk,
-          int32_t per, v4u *__restrict__ out, int32_t *status) {
+          const int32_t *__restrict__ row_of_slot, int64_t T, int32_t k, int32_t nch,
+          v4u *__restrict__ out, int32_t *status) {
+  const int lane = lane_id();
+  const int nblk = (nch + kCbLaneChunks * kWave - 1) / (kCbLaneChunks * kWave);
+  const int64_t n_units = T * nblk;
+  const int64_t nw = static_cast<int64_t>(gridDim.x) * kCbWaves;
+  for (int64_t unit = static_cast<int64_t>(blockIdx.x) * kCbWaves + threadIdx.x / kWave;
+       unit < n_units; unit += nw) {
+    const int64_t t = unit / nblk;
+    const int b = static_cast<int>(unit - t * nblk);
+    int row;
+    float g;
+    token_rows(row_of_slot, gate, t, k, lane, n_rows, status, row, g);
+    const int c_end = min(nch, (b + 1) * kCbLaneChunks * kWave);
+    for (int c0 = b * kCbLaneChunks * kWave + lane; c0 < c_end; c0 += kCbChunks * kWave) {
+      v4u v[kCbChunks][kCbRows];
+#pragma unroll
+      for (int kk = 0; kk < kCbRows; ++kk) {
+        const int r = kk < k ? readlane(row, kk) : -1;
+#pragma unroll
+        for (int u = 0; u < kCbChunks; ++u) {
+          const int cc = c0 + u * kWave;
+          if (r >= 0 && cc < c_end)
+            v[u][kk] = __builtin_nontemporal_load(y + static_cast<int64_t>(r) * nch + cc);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kCbChunks; ++u) {
+        const int cc = c0 + u * kWave;
+        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < kCbRows; ++kk) {
+          const int r = kk < k ? readlane(row, kk) : -1;
+          if (r >= 0 && cc < c_end)
+            acc_chunk(acc, __int_as_float(readlane(__float_as_int(g), kk)), v[u][kk]);
+        }
+        if (cc < c_end) __builtin_nontemporal_store(pack_chunk(acc), out + t * nch + cc);
+      }
+    }
+  }
+}
+
+// k > kCbRows: up to kCh 16-byte chunks per lane of one token's row, `per`
+// chunks in all (nblk equal units per row); the loads of kCbRows rows are in
+// flight together, then those of the next group.
+template <int kCh>
+__global__ void __launch_bounds__(kCbThreads)
+k_combine_many(const v4u *__restrict__ y, int64_t n_rows, const float *__restrict__ gate,
+               const int32_t *__restrict__ row_of_slot, int64_t T, int32_t k, int32_t nch,
+               int32_t nblk, int32_t per, v4u *__restrict__ out, int32_t *status) {
   const int lane = lane_id();
   const int64_t n_units = T * nblk;
   const int64_t nw = static_cast<int64_t>(gridDim.x) * kCbWaves;
@@ -99,7 +147,7 @@ k_combine(const v4u *__restrict__ y, int64_t n_rows, const float *__restrict__ g
     token_rows(row_of_slot, gate, t, k, lane, n_rows, status, row, g);
     const int c0 = b * per + lane, c_end = min(nch, (b + 1) * per);
     float acc[kCh][8] = {};
-    for (int k0 = 0; k0 < (kMany ? k : 1); k0 += kCbRows) {
+    for (int k0 = 0; k0 < k; k0 += kCbRows) {
       v4u v[kCh][kCbRows];
 #pragma unroll
       for (int kk = 0; kk < kCbRows; ++kk) {
@@ -113,39 +161,37 @@ k_combine(const v4u *__restrict__ y, int64_t n_rows, const float *__restrict__ g
       }
 #pragma unroll
       for (int u = 0; u < kCh; ++u) {
-        const int cc = c0 + u * kWave;
 #pragma unroll
         for (int kk = 0; kk < kCbRows; ++kk) {
           const int r = k0 + kk < k ? readlane(row, k0 + kk) : -1;
-          if (r >= 0 && cc < c_end)
+          if (r >= 0 && c0 + u * kWave < c_end)
             acc_chunk(acc[u], __int_as_float(readlane(__float_as_int(g), k0 + kk)), v[u][kk]);
         }
-        if (!kMany && cc < c_end)
-          __builtin_nontemporal_store(pack_chunk(acc[u]), out + t * nch + cc);
       }
     }
 #pragma unroll
     for (int u = 0; u < kCh; ++u) {
       const int cc = c0 + u * kWave;
-      if (kMany && cc < c_end)
-        __builtin_nontemporal_store(pack_chunk(acc[u]), out + t * nch + cc);
+      if (cc < c_end) __builtin_nontemporal_store(pack_chunk(acc[u]), out + t * nch + cc);
     }
   }
 }
 
-template <int kCh, bool kMany>
-static void start_combine(const v4u *y, int64_t n_rows, const float *gate,
-                          const int32_t *row_of_slot, int64_t T, int32_t k, int32_t nch, v4u *out,
-                          int32_t *status, hipStream_t stream) {
+static dim3 combine_grid(int64_t units) {
+  const int64_t need = (units + kCbWaves - 1) / kCbWaves;
+  return dim3(static_cast<unsigned>(need < kCbGrid ? need : kCbGrid));
+}
+
+template <int kCh>
+static void start_many(const v4u *y, int64_t n_rows, const float *gate, const int32_t *row_of_slot,
+                       int64_t T, int32_t k, int32_t nch, v4u *out, int32_t *status,
+                       hipStream_t stream) {
   // equal units per row, so that a row a little over a multiple of the
-  // unit's width leaves no nearly empty wave; in whole 128-byte lines (units
-  // that cut lines took 10.2 us against 9.5 on 346 tokens, H = 12128, k = 4)
+  // unit's width leaves no nearly empty wave; in whole 128-byte lines
   const int32_t nblk = (nch + kCh * kWave - 1) / (kCh * kWave);
   const int32_t per = ((nch + nblk - 1) / nblk + 7) / 8 * 8;
-  const int64_t need = (T * nblk + kCbWaves - 1) / kCbWaves;
-  const dim3 grid(static_cast<unsigned>(need < kCbGrid ? need : kCbGrid));
-  hipLaunchKernelGGL((k_combine<kCh, kMany>), grid, dim3(kCbThreads), 0, stream, y, n_rows, gate,
-                     row_of_slot, T, k, nch, nblk, per, out, status);
+  hipLaunchKernelGGL(k_combine_many<kCh>, combine_grid(T * nblk), dim3(kCbThreads), 0, stream, y,
+                     n_rows, gate, row_of_slot, T, k, nch, nblk, per, out, status);
 }
 
 hipError_t launch_combine(const uint16_t *y, int64_t n_rows, const float *gate,
@@ -162,11 +208,14 @@ hipError_t launch_combine(const uint16_t *y, int64_t n_rows, const float *gate,
   // T = 16000) 46.4 / 40.5.
   const int64_t ones = (nch + kWave - 1) / kWave;
   if (k <= kCbRows)
-    start_combine<2, false>(ys, n_rows, gate, row_of_slot, T, k, nch, os, status, stream);
+    hipLaunchKernelGGL(k_combine,
+                       combine_grid(T * ((nch + kCbLaneChunks * kWave - 1) / (kCbLaneChunks * kWave))),
+                       dim3(kCbThreads), 0, stream, ys, n_rows, gate, row_of_slot, T, k, nch, os,
+                       status);
   else if (20 * static_cast<int64_t>(nch) >= 19 * kWave * ones)
-    start_combine<1, true>(ys, n_rows, gate, row_of_slot, T, k, nch, os, status, stream);
+    start_many<1>(ys, n_rows, gate, row_of_slot, T, k, nch, os, status, stream);
   else
-    start_combine<2, true>(ys, n_rows, gate, row_of_slot, T, k, nch, os, status, stream);
+    start_many<2>(ys, n_rows, gate, row_of_slot, T, k, nch, os, status, stream);
   return hipGetLastError();
 }
 
