@@ -38,6 +38,7 @@ namespace uep {
 
 constexpr int kMaxE = 1024;
 constexpr int kMaxR = 64;
+constexpr int kEntRegs = 4;                // entries per lane of the first 256 experts
 constexpr int kMaxRec = 256;               // R * n_slot: one transfer per slot at most
 constexpr int kDepth = 10;                 // bisection levels per round
 constexpr int kNodes = (1 << kDepth) - 1;  // probes per round
@@ -55,22 +56,26 @@ constexpr int kCopies = 8;
 static_assert(kHdr <= kHdrSpan && kBitWords * 8 == 128, "outcome copies are whole lines");
 
 struct PlanWs {
-  int64_t *hdr;        // [4] tau_lo0, tau_hi0, L, status, then per round j the
-                       // bisection state after rounds 0..j: lo, hi, best, probes
-  uint64_t *bits;      // [kRounds][kCopies][kBitWords] feasible probes, one bit per node
-  int32_t *ell;        // [R]
-  int32_t *rank_desc;  // [R] ranks by descending load (visiting order)
-  int32_t *rank_asc;   // [R] ranks by ascending load (target order)
-  int32_t *eorder;     // [E] experts of each rank, descending load
-  int32_t *elam;       // [E] their loads
-  int32_t *lam;        // [E] lambda_e
-  int32_t *res;        // [kRounds][kNodes] probe outcome
-  uint32_t *rec;       // [kRounds][kNodes][2 * RS] (e | t << 16, delta) pairs
+  int64_t *hdr;    // [4] tau_lo0, tau_hi0, L, status, then per round j the
+                   // bisection state after rounds 0..j: lo, hi, best, probes
+  uint64_t *bits;  // [kRounds][kCopies][kBitWords] feasible probes, one bit per node
+  v4i *rank;       // [kMaxR] i-th rank of the visiting order (descending load):
+                   // its load and its largest expert load; i-th rank of the
+                   // target order (ascending load): rank and load; 0 past R
+  uint2 *ent;      // [E] (load, expert) in visiting order: rank by rank, each
+                   // rank's main experts by descending load
+  int32_t *ell;    // [R]
+  int32_t *lam;    // [E] lambda_e
+  int32_t *res;    // [kRounds][kNodes] probe outcome
+  uint32_t *rec;   // [kRounds][kNodes][2 * RS] (e | t << 16, delta) pairs
 };
+
+constexpr int64_t even(int64_t n) { return (n + 1) / 2 * 2; }
 
 size_t plan_ws_bytes(int32_t R, int32_t E, int32_t NS) {
   const int64_t RS = static_cast<int64_t>(R) * NS;
-  const int64_t ints = 3 * R + 3 * E + int64_t(kRounds) * kNodes * (1 + 2 * RS);
+  const int64_t ints = 4 * kMaxR + 2 * E + even(R) + even(E) + even(kRounds * kNodes) +
+                       int64_t(kRounds) * kNodes * 2 * RS;
   return static_cast<size_t>(kHdrSpan * 8 + kRounds * kCopies * kBitWords * 8 +
                              (ints * 4 + 255) / 256 * 256);
 }
@@ -80,21 +85,15 @@ static PlanWs carve(void *ws, int32_t R, int32_t E, int32_t NS) {
   PlanWs w;
   w.hdr = static_cast<int64_t *>(ws);
   w.bits = reinterpret_cast<uint64_t *>(w.hdr + kHdrSpan);
-  int32_t *p = reinterpret_cast<int32_t *>(w.bits + kRounds * kCopies * kBitWords);
+  w.rank = reinterpret_cast<v4i *>(w.bits + kRounds * kCopies * kBitWords);
+  w.ent = reinterpret_cast<uint2 *>(w.rank + kMaxR);
+  int32_t *p = reinterpret_cast<int32_t *>(w.ent + E);
   w.ell = p;
-  p += R;
-  w.rank_desc = p;
-  p += R;
-  w.rank_asc = p;
-  p += R;
-  w.eorder = p;
-  p += E;
-  w.elam = p;
-  p += E;
+  p += even(R);
   w.lam = p;
-  p += E;
+  p += even(E);
   w.res = p;
-  p += kRounds * kNodes;
+  p += even(kRounds * kNodes);
   w.rec = reinterpret_cast<uint32_t *>(p);
   return w;
 }
@@ -122,6 +121,8 @@ __device__ __forceinline__ double readlane_d(double v, int l) {
 __global__ void __launch_bounds__(kPrepThreads) k_plan_prep(PlanArgs a) {
   __shared__ int32_t s_lam[kMaxE];
   __shared__ int32_t s_ell[kMaxR];
+  __shared__ int32_t s_top[kMaxR];  // largest expert load of each rank
+  __shared__ int32_t s_pos[kMaxR];  // place of each rank in the visiting order
   __shared__ int64_t s_part[kPrepThreads];
   __shared__ unsigned long long s_L;
   __shared__ int32_t s_bad;
@@ -183,23 +184,25 @@ __global__ void __launch_bounds__(kPrepThreads) k_plan_prep(PlanArgs a) {
     s_ell[tid] = s;
     a.ws.ell[tid] = s;
   }
-  if (tid < E) {  // each rank's main experts by descending load (ties: lower id)
-    const int r = tid / nm, l = s_lam[tid];
-    int pos = 0;
+  // each rank's main experts by descending load (ties: lower id)
+  int pos = 0, le = 0;
+  if (tid < E) {
+    const int r = tid / nm;
+    le = s_lam[tid];
     for (int j = r * nm; j < r * nm + nm; ++j) {
       const int lj = s_lam[j];
-      pos += (lj > l) || (lj == l && j < tid);
+      pos += (lj > le) || (lj == le && j < tid);
     }
-    a.ws.eorder[r * nm + pos] = tid;
-    a.ws.elam[r * nm + pos] = l;
+    if (pos == 0) s_top[r] = le;
   }
   __syncthreads();
   {  // ranks by descending and by ascending load (ties: lower rank): 16
      // threads per rank each compare it with 4 others, then a DPP row sum
     const int i = tid >> 4, part = tid & 15;
     int cnt = 0;  // ranks ahead in descending order << 16 | ahead in ascending
+    int li = 0;
     if (i < R) {
-      const int li = s_ell[i];
+      li = s_ell[i];
 #pragma unroll
       for (int k = 0; k < kMaxR / 16; ++k) {
         const int r = part * (kMaxR / 16) + k;
@@ -211,11 +214,17 @@ __global__ void __launch_bounds__(kPrepThreads) k_plan_prep(PlanArgs a) {
       }
     }
     cnt = row_sum(cnt);
-    if (i < R && part == 0) {
-      a.ws.rank_desc[cnt >> 16] = i;
-      a.ws.rank_asc[cnt & 0xFFFF] = i;
+    if (part == 0) {
+      const int dn = i < R ? cnt >> 16 : i, up = i < R ? cnt & 0xFFFF : i;
+      if (i < R) s_pos[i] = dn;
+      int2 *rk = reinterpret_cast<int2 *>(a.ws.rank);
+      rk[2 * dn] = i < R ? make_int2(li, s_top[i]) : make_int2(0, 0);
+      rk[2 * up + 1] = i < R ? make_int2(i, li) : make_int2(0, 0);
     }
   }
+  __syncthreads();
+  if (tid < E)
+    a.ws.ent[s_pos[tid / nm] * nm + pos] = make_uint2(static_cast<uint32_t>(le), static_cast<uint32_t>(tid));
   if (tid < kWave) {
     const int hi = wave_max(tid < R ? s_ell[tid] : -1);
     if (tid == 0) {
@@ -255,193 +264,159 @@ __device__ __forceinline__ int wave_shl1(int v) {
 // The experts are visited in one flat loop (rank by rank, experts by
 // descending load) with scalar loop state.
 
-// Loads experts [j0, j0 + 64) of rank r's visiting order into lanes.
-// Lanes past the rank's last expert read that expert and hold zeros: no
-// divergent branch in the probes' loops.
-__device__ __forceinline__ void load_experts(const PlanArgs &a, int r, int j0, int lane,
-                                             const int32_t *s_eorder, const int32_t *s_elam,
-                                             int &ev, int &lv) {
-  const int jl = j0 + lane;
-  const int i = r * a.nm + min(jl, a.nm - 1);
-  const int v = s_eorder[i], l = s_elam[i];
-  ev = jl < a.nm ? v : 0;
-  lv = jl < a.nm ? l : 0;
+// A probe is one dependent chain on one wave, and on this chip an instruction
+// of such a chain costs 8 cycles, a readlane with a computed lane or a
+// ballot with its population count about 35, and a branch about 25, so the
+// loops below keep a visit to one ballot, a few readlanes and three branches:
+// the excess x and the first expert's need of every overloaded rank sit in
+// lanes, the failure tests are one sign test, and an expert is recorded by its
+// place in the visiting order.  A visit takes about 200-240 ns (420 ns with a
+// branch per test and an LDS fetch of the experts per rank).  Code that runs
+// once costs about 85 ns per 64 bytes to fetch, so it is kept short.
+struct Probe {
+  int tau, lane;
+  int nover;         // overloaded ranks: the first nover of the visiting order
+  int xv, nv;        // lane i: excess of the i-th, and min(excess, largest load)
+  int as_r, as_l;    // lane i: i-th target rank and its load
+  const uint2 *ent;  // (load, expert) in visiting order
+};
+
+// After a visit that left x of the excess: the rank's next expert, or the
+// next rank, whose excess and need are xn and nn.  ok counts up to 0 ranks
+// left and is 1 when a rank's experts ran out.
+__device__ __forceinline__ void next_visit(const Probe &s, int nm, int &x, int &need, int &p,
+                                           int &end, int &oi, int &ok, int xn, int nn) {
+  if (x > 0) {
+    ++p;
+    need = min(x, uni(static_cast<int>(s.ent[min(p, end - 1)].x)));
+    ok = p == end ? 1 : ok;
+  } else {
+    x = xn;
+    need = nn;
+    p = end;
+    end += nm;
+    ++oi;
+    ++ok;
+  }
 }
 
 // One redundant slot per rank: every transfer uses up its target, so
 // transfer k goes to the k-th listed target and its record stays in lane k.
 // The slacks never change, so P is the fixed inclusive prefix of the list
-// and the lanes with P - B < need are the prefix [0, hh) (lanes before the
-// head have P <= B): the whole targets are [h, hh).
+// (m and Q = P - m its slacks and exclusive prefix) and the lanes with
+// P < B + need are the prefix [0, hh) (lanes before the head have P <= B, and
+// the lanes past the list have P = the total, which is below B + need only
+// if every target is whole): the whole targets are [h, hh).  The list is
+// sorted, so a whole target below u_min shows as hh past the nbig targets of
+// at least u_min.
 template <int kSite>
-__device__ __forceinline__ int probe_one_slot(const PlanArgs &a, int tau, int lane, int rk_r, int rk_l,
-                              int as_r, int as_l, const int32_t *s_eorder,
-                              const int32_t *s_elam, uint32_t *s_re, int32_t *s_rd) {
-  const int R = a.R, nm = a.nm, u_min = a.u_min;
-  const bool tv = lane < R && as_l < tau;
-  const int m = tv ? tau - as_l : 0;
-  const uint64_t tmask = ballot(tv);  // a prefix of the lanes
+__device__ __forceinline__ int probe_one_slot(const PlanArgs &a, const Probe &s, uint2 *rec) {
+  const int nm = a.nm, u_min = a.u_min, lane = s.lane;
+  const bool tv = lane < a.R && s.as_l < s.tau;
+  const int m = tv ? s.tau - s.as_l : 0;
   // inclusive prefix of the slacks: each is below 2^25, the sum below 2^31
-  int P = m;
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int t = __shfl_up(P, o);
-    if (lane >= o) P += t;
-  }
-  const uint64_t low_umin = ballot(tv && m < u_min);
-  int x = readlane(rk_l, 0) - tau;
-  if (x <= 0) return 0;  // nothing to shed
-  int r = readlane(rk_r, 0);
-  int ev, lv;
-  load_experts(a, r, 0, lane, s_eorder, s_elam, ev, lv);
-  int rec_e = 0, rec_d = 0;
-  int h = 0, B = 0, oi = 0, j = 0;  // head, slack before it, rank, expert
-  bool fail = false;
-  for (;;) {
-    const int c = readlane(lv, j & (kWave - 1));
-    const int e = readlane(ev, j & (kWave - 1));
-    const int need = min(x, c);
-    const uint64_t wm = ballot(P - B < need) & tmask;
-    const int hh = __popcll(wm);
-    const int Ph = readlane(P, hh & (kWave - 1)), mh = readlane(m, hh & (kWave - 1));
-    const int taken = Ph - mh - B;  // slack of the whole targets
-    const int d = need - taken;     // the rest, at most mh
-    x -= taken;
-    const int take = d >= u_min ? 1 : 0;
+  const int P = wave_scan_incl(m), Q = P - m;
+  const int last = __popcll(ballot(tv)) - 1, nbig = __popcll(ballot(tv && m >= u_min));
+  int rec_p = 0, rec_d = 0;
+  int h = 0, B = 0;  // head, slack before it
+  int oi = 0, p = 0, end = nm, x = readlane(s.xv, 0), need = readlane(s.nv, 0), ok = -s.nover;
+  while (ok < 0) {
+    const int xn = readlane(s.xv, (oi + 1) & (kWave - 1)), nn = readlane(s.nv, (oi + 1) & (kWave - 1));
+    const int hh = __popcll(ballot(static_cast<uint32_t>(P) < static_cast<uint32_t>(B + need)));
+    const int Qh = readlane(Q, hh & (kWave - 1)), mh = readlane(m, hh & (kWave - 1));
+    const int d = need - (Qh - B);  // the rest after the whole targets, at most mh
+    x -= Qh - B;
     // an expert with no load left, no target for the rest (every target
     // whole), a whole target below u_min, or a rest below u_min that is not
     // only this expert's shortfall (max(d, min(x, mh)) < u_min)
-    fail = c <= 0 || wm == tmask || ((wm & low_umin) >> (h & (kWave - 1))) != 0 ||
-           max(d, min(x, mh)) < u_min;
-    if (fail) break;
+    const int bad = (need - 1) | (min(max(h, nbig), last) - hh) | (max(d, min(x, mh)) - u_min);
     // the whole targets and, when the rest is taken, target hh
+    const int take = 1 + ((d - u_min) >> 31);  // d >= u_min, in scalar integers
     const bool mine = static_cast<uint32_t>(lane - h) < static_cast<uint32_t>(hh - h + take);
-    rec_e = mine ? e : rec_e;
+    rec_p = mine ? p : rec_p;
     rec_d = mine ? (lane == hh ? d : m) : rec_d;
-    x -= take ? d : 0;
-    B = take ? Ph : Ph - mh;
+    x -= d & -take;
+    B = Qh + (mh & -take);
     h = hh + take;
-    if (x > 0) {
-      if (++j < nm) {  // next expert of this rank
-        if ((j & (kWave - 1)) == 0) load_experts(a, r, j, lane, s_eorder, s_elam, ev, lv);
-        continue;
-      }
-      fail = true;  // the rank's experts ran out
-      break;
-    }
-    if (++oi >= R) break;
-    x = readlane(rk_l, oi) - tau;
-    if (x <= 0) break;  // the remaining ranks are not overloaded
-    r = readlane(rk_r, oi);
-    load_experts(a, r, 0, lane, s_eorder, s_elam, ev, lv);
-    j = 0;
+    next_visit(s, nm, x, need, p, end, oi, ok, xn, nn);
+    ok = bad < 0 ? 1 : ok;
   }
-  if (fail) return -1;
-  if (lane < h) {
-    s_re[lane] = static_cast<uint32_t>(rec_e) | (static_cast<uint32_t>(as_r) << 16);
-    s_rd[lane] = rec_d;
-  }
+  if (ok > 0) return -1;
+  if (lane < h)
+    rec[lane] = make_uint2(s.ent[rec_p].y | (static_cast<uint32_t>(s.as_r) << 16),
+                           static_cast<uint32_t>(rec_d));
   return h;
 }
 
 // Several redundant slots per rank: a target that keeps slack and a free
 // slot after an expert's last (partial) transfer moves back to its place in
-// the list; the lanes it passes shift down by one (DPP) and P is patched.
-// The list entries are packed keys (slack << 6) | (63 - rank).  P is
-// nondecreasing over the live lanes, and every lane before the head has
-// P <= B, so the lanes with P - B < need are the prefix [0, hh): hh is the
-// population count of one ballot, and the whole targets are [h, hh).  In
-// the loop a record is (e, key of the transfer: amount << 6 | 63 - rank),
-// written by the lanes of the targets themselves; the records are put into
-// the common (e | rank << 16, amount) form once the probe has succeeded.
+// the list; the lanes it passes shift down by one (DPP) and the prefixes are
+// patched.  The list entries are packed keys (slack << 6) | (63 - rank), in
+// descending order over all lanes (the consumed ones before the head keep
+// theirs), so one ballot and a population count find places in it.  In the
+// loop a record is (place of the expert, key of the transfer: amount << 6 |
+// 63 - rank), written to s_rec by the lanes of the targets themselves; the
+// records are put into the common form once the probe has succeeded.
 template <int kSite>
-__device__ __forceinline__ int probe_multi(const PlanArgs &a, int tau, int lane, int rk_r, int rk_l,
-                           int as_r, int as_l, const int32_t *s_eorder,
-                           const int32_t *s_elam, uint32_t *s_re, int32_t *s_rd) {
-  const int R = a.R, nm = a.nm, NS = a.NS, u_min = a.u_min;
-  const bool tv = lane < R && as_l < tau && NS > 0;
-  int key = tv ? ((tau - as_l) << 6) | (kWave - 1 - as_r) : 0;
+__device__ __forceinline__ int probe_multi(const PlanArgs &a, const Probe &s, uint2 *s_rec,
+                                           uint2 *rec) {
+  const int NS = a.NS, nm = a.nm, u_min = a.u_min, lane = s.lane;
+  const bool tv = lane < a.R && s.as_l < s.tau && NS > 0;
+  int m = tv ? s.tau - s.as_l : 0;
+  int key = tv ? (m << 6) | (kWave - 1 - s.as_r) : 0;
   int used = 0;
-  const uint64_t live = ballot(tv);  // a prefix of the lanes; its length never changes
-  int P = key >> 6;
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int t = __shfl_up(P, o);
-    if (lane >= o) P += t;
-  }
-  // live lanes whose slack is below u_min (refreshed when a key moves)
-  uint64_t low = ballot((key >> 6) < u_min);
-  int x = readlane(rk_l, 0) - tau;
-  if (x <= 0) return 0;
-  int r = readlane(rk_r, 0);
-  int ev, lv;
-  load_experts(a, r, 0, lane, s_eorder, s_elam, ev, lv);
-  int h = 0, B = 0, n = 0, oi = 0, j = 0;
-  bool fail = false;
-  for (;;) {
-    const int c = readlane(lv, j & (kWave - 1));
-    const int e = readlane(ev, j & (kWave - 1));
-    const int need = min(x, c);
-    const uint64_t wm = ballot(P - B < need) & live;
-    const int hh = __popcll(wm);
-    const int Ph = readlane(P, hh & (kWave - 1)), kh = readlane(key, hh & (kWave - 1));
+  int P = wave_scan_incl(m), Q = P - m;
+  const int last = __popcll(ballot(tv)) - 1;  // the list's length never changes
+  int nbig = __popcll(ballot(tv && m >= u_min));
+  int h = 0, B = 0, n = 0;
+  int oi = 0, p = 0, end = nm, x = readlane(s.xv, 0), need = readlane(s.nv, 0), ok = -s.nover;
+  while (ok < 0) {
+    const int xn = readlane(s.xv, (oi + 1) & (kWave - 1)), nn = readlane(s.nv, (oi + 1) & (kWave - 1));
+    const int hh = __popcll(ballot(static_cast<uint32_t>(P) < static_cast<uint32_t>(B + need)));
+    const int Qh = readlane(Q, hh & (kWave - 1)), kh = readlane(key, hh & (kWave - 1));
+    const int uh = readlane(used, hh & (kWave - 1)) + 1;
     const int mh = kh >> 6;
-    const int taken = Ph - mh - B;  // slack of the whole targets
-    const int d = need - taken;     // the rest, at most mh
-    x -= taken;
-    const int take = d >= u_min ? 1 : 0;
-    // an expert with no load left, no target for the rest (every live lane
-    // whole), a whole target below u_min, or a rest below u_min that is not
-    // only this expert's shortfall (max(d, min(x, mh)) < u_min)
-    fail = c <= 0 || wm == live || ((wm & low) >> (h & (kWave - 1))) != 0 ||
-           max(d, min(x, mh)) < u_min;
-    if (fail) break;
-    const int nw = hh - h + take;
-    {  // the other lanes write a spare area past the records
-      const int at = static_cast<uint32_t>(lane - h) < static_cast<uint32_t>(nw) ? n + lane - h
-                                                                             : kMaxRec + lane;
-      s_re[at] = static_cast<uint32_t>(e);
-      s_rd[at] = lane == hh ? ((d << 6) | (key & (kWave - 1))) : key;
+    const int d = need - (Qh - B);
+    x -= Qh - B;
+    // as in probe_one_slot
+    const int bad = (need - 1) | (min(max(h, nbig), last) - hh) | (max(d, min(x, mh)) - u_min);
+    const int take = 1 + ((d - u_min) >> 31);  // d >= u_min, in scalar integers
+    {  // the other lanes write a spare area past the records (n <= kMaxRec)
+      const int o = lane - h;
+      const int at = static_cast<uint32_t>(o) < static_cast<uint32_t>(hh - h + take)
+                         ? n + o
+                         : kMaxRec + lane;
+      s_rec[at] = make_uint2(
+          static_cast<uint32_t>(p),
+          static_cast<uint32_t>(lane == hh ? (d << 6) | (key & (kWave - 1)) : key));
     }
-    n += nw;
-    B = Ph - mh;
-    h = hh;
-    if (take) {
-      x -= d;
-      const int uh = readlane(used, hh) + 1;
-      if (mh == d || uh >= NS) {  // out of slack or slots: leaves the list
-        B = Ph;
-        h = hh + 1;
-      } else {  // back to its place: after every key still larger
-        const int nk = ((mh - d) << 6) | (kh & (kWave - 1));
-        const int p = hh + __popcll(ballot(key > nk) & (~uint64_t(1) << hh) & live);
-        const bool mv = static_cast<uint32_t>(lane - hh) < static_cast<uint32_t>(p - hh);
-        const int ks = wave_shl1(key), us = wave_shl1(used), ps = wave_shl1(P);
-        key = mv ? ks : (lane == p ? nk : key);
-        used = mv ? us : (lane == p ? uh : used);
-        P = mv ? ps - mh : (lane >= p ? P - d : P);
-        low = ballot((key >> 6) < u_min);
-      }
+    n += hh - h + take;
+    x -= d & -take;
+    // out of slack or slots: target hh leaves the list, else a used one goes
+    // back to its place, after every key still larger
+    const int out = take & (((mh - d - 1) >> 31) | ((NS - 1 - uh) >> 31));
+    B = Qh + (mh & -out);
+    h = hh + out;
+    if (take > out) {
+      const int nk = ((mh - d) << 6) | (kh & (kWave - 1));
+      const int to = __popcll(ballot(key > nk)) - 1;
+      const bool mv = static_cast<uint32_t>(lane - hh) < static_cast<uint32_t>(to - hh);
+      const int ks = wave_shl1(key), us = wave_shl1(used), ps = wave_shl1(P);
+      key = mv ? ks : (lane == to ? nk : key);
+      used = mv ? us : (lane == to ? uh : used);
+      P = mv ? ps - mh : (lane >= to ? P - d : P);
+      m = key >> 6;
+      Q = P - m;
+      nbig = __popcll(ballot(m >= u_min));
     }
-    if (x > 0) {
-      if (++j < nm) {  // next expert of this rank
-        if ((j & (kWave - 1)) == 0) load_experts(a, r, j, lane, s_eorder, s_elam, ev, lv);
-        continue;
-      }
-      fail = true;  // the rank's experts ran out
-      break;
-    }
-    if (++oi >= R) break;
-    x = readlane(rk_l, oi) - tau;
-    if (x <= 0) break;  // the remaining ranks are not overloaded
-    r = readlane(rk_r, oi);
-    load_experts(a, r, 0, lane, s_eorder, s_elam, ev, lv);
-    j = 0;
+    next_visit(s, nm, x, need, p, end, oi, ok, xn, nn);
+    ok = bad < 0 ? 1 : ok;
   }
-  if (fail) return -1;
+  if (ok > 0) return -1;
   __syncthreads();
   for (int i = lane; i < n; i += kWave) {
-    const int k = s_rd[i];
-    s_re[i] |= static_cast<uint32_t>(kWave - 1 - (k & (kWave - 1))) << 16;
-    s_rd[i] = k >> 6;
+    const uint2 v = s_rec[i];
+    rec[i] = make_uint2(s.ent[v.x].y | ((kWave - 1 - (v.y & (kWave - 1))) << 16), v.y >> 6);
   }
   return n;
 }
@@ -450,47 +425,38 @@ __device__ __forceinline__ int probe_multi(const PlanArgs &a, int tau, int lane,
 // and slot count, and the target is a wave max plus a ballot for the lowest
 // rank among ties.
 template <int kSite>
-__device__ __forceinline__ int probe_wide(const PlanArgs &a, int tau, int lane, int rk_r, int rk_l,
-                          int ell_lane, const int32_t *s_eorder, const int32_t *s_elam,
-                          uint32_t *s_re, int32_t *s_rd) {
-  int slk = lane < a.R ? max(tau - ell_lane, 0) : 0;
+__device__ __forceinline__ int probe_wide(const PlanArgs &a, const Probe &s, uint2 *rec) {
+  const int lane = s.lane;
+  int slk = lane < a.R ? max(s.tau - a.ws.ell[lane], 0) : 0;
   int used = 0;
   int n = 0;
-  for (int oi = 0; oi < a.R; ++oi) {
-    int exc = readlane(rk_l, oi) - tau;
-    if (exc <= 0) break;
-    const int r = readlane(rk_r, oi);
-    for (int j0 = 0; j0 < a.nm && exc > 0; j0 += kWave) {
-      const int jl = j0 + lane;
-      const int ev = jl < a.nm ? s_eorder[r * a.nm + jl] : 0;
-      const int lv = jl < a.nm ? s_elam[r * a.nm + jl] : 0;
-      const int jn = min(kWave, a.nm - j0);
-      for (int j = 0; j < jn && exc > 0; ++j) {
-        const int e = readlane(ev, j);
-        int cap = readlane(lv, j);
-        while (exc > 0 && cap > 0) {
-          const bool ok = slk > 0 && used < a.NS;
-          const int v = ok ? slk : 0;
-          const int m = wave_max(v);
-          if (m == 0) return -1;
-          const int ts = uni(__ffsll(static_cast<unsigned long long>(ballot(v == m && ok))) - 1);
-          const int d = min(min(exc, m), cap);
-          if (d < a.u_min) {
-            if (min(exc, m) < a.u_min) return -1;
-            break;
-          }
-          if (lane == ts) {
-            slk -= d;
-            ++used;
-          }
-          if (lane == 0) {
-            s_re[n] = static_cast<uint32_t>(e) | (static_cast<uint32_t>(ts) << 16);
-            s_rd[n] = d;
-          }
-          ++n;
-          exc -= d;
-          cap -= d;
+  for (int oi = 0; oi < s.nover; ++oi) {
+    int exc = readlane(s.xv, oi);
+    for (int j = 0; j < a.nm && exc > 0; ++j) {
+      const uint2 v = s.ent[oi * a.nm + j];
+      const int e = uni(static_cast<int>(v.y));
+      int cap = uni(static_cast<int>(v.x));
+      while (exc > 0 && cap > 0) {
+        const bool ok = slk > 0 && used < a.NS;
+        const int sv = ok ? slk : 0;
+        const int m = wave_max(sv);
+        if (m == 0) return -1;
+        const int ts = uni(__ffsll(static_cast<unsigned long long>(ballot(sv == m && ok))) - 1);
+        const int d = min(min(exc, m), cap);
+        if (d < a.u_min) {
+          if (min(exc, m) < a.u_min) return -1;
+          break;
         }
+        if (lane == ts) {
+          slk -= d;
+          ++used;
+        }
+        if (lane == 0)
+          rec[n] = make_uint2(static_cast<uint32_t>(e) | (static_cast<uint32_t>(ts) << 16),
+                              static_cast<uint32_t>(d));
+        ++n;
+        exc -= d;
+        cap -= d;
       }
     }
     if (exc > 0) return -1;
@@ -498,18 +464,27 @@ __device__ __forceinline__ int probe_wide(const PlanArgs &a, int tau, int lane, 
   return n;
 }
 
-// One probe at tau with the variant the thresholds and slots allow.  kSite
-// gives every call site its own copy: shared by two kernels, the compiler
-// loses sight of the probes' scalar loop state.
+// One probe at tau with the variant the thresholds and slots allow; a
+// feasible one leaves its transfers in rec as (e | rank << 16, amount).  rk =
+// this lane's entry of PlanWs::rank.  At least one rank is not overloaded
+// (tau is no less than the mean), so nover < R.  kSite gives every call site
+// its own copy: shared by two kernels, the compiler loses sight of the
+// probes' scalar loop state.
 template <int kSite>
-__device__ __forceinline__ int run_probe(const PlanArgs &a, bool packed, int tau, int lane,
-                                         int rk_r, int rk_l, int as_r, int as_l, int ell_lane,
-                                         const int32_t *s_eorder, const int32_t *s_elam,
-                                         uint32_t *s_re, int32_t *s_rd) {
-  if (!packed) return probe_wide<kSite>(a, tau, lane, rk_r, rk_l, ell_lane, s_eorder, s_elam, s_re, s_rd);
-  if (a.NS == 1)
-    return probe_one_slot<kSite>(a, tau, lane, rk_r, rk_l, as_r, as_l, s_eorder, s_elam, s_re, s_rd);
-  return probe_multi<kSite>(a, tau, lane, rk_r, rk_l, as_r, as_l, s_eorder, s_elam, s_re, s_rd);
+__device__ __forceinline__ int run_probe(const PlanArgs &a, bool packed, int tau, int lane, v4i rk,
+                                         const uint2 *ent, uint2 *s_rec, uint2 *rec) {
+  Probe s;
+  s.tau = tau;
+  s.lane = lane;
+  s.xv = rk.x - tau;
+  s.nv = min(s.xv, rk.y);
+  s.nover = __popcll(ballot(lane < a.R && s.xv > 0));
+  s.as_r = rk.z;
+  s.as_l = rk.w;
+  s.ent = ent;
+  if (!packed) return probe_wide<kSite>(a, s, rec);
+  if (a.NS == 1) return probe_one_slot<kSite>(a, s, rec);
+  return probe_multi<kSite>(a, s, s_rec, rec);
 }
 
 // Bisection state before round rd: the initial interval, or the state
@@ -528,84 +503,81 @@ __device__ __forceinline__ BisState state_before(const PlanArgs &a, int rd) {
   return {lo, hi, rd == 0 ? -1 : static_cast<int>(best), rd == 0 ? 0 : static_cast<int>(probes)};
 }
 
-__device__ __forceinline__ uint64_t readlane64(uint64_t v, int l) {
-  const uint32_t lo = static_cast<uint32_t>(readlane(static_cast<int>(v), l));
-  const uint32_t hi = static_cast<uint32_t>(readlane(static_cast<int>(v >> 32), l));
-  return (static_cast<uint64_t>(hi) << 32) | lo;
-}
-
-// Round rd's outcome words: the kCopies copies of word w into lane w (the
-// lanes past the last word read it too).  No branch between the loads, so
-// that they stay in flight together with the kernel's other inputs.
-__device__ __forceinline__ void outcome_load(const PlanArgs &a, int rd, uint64_t (&v)[kCopies]) {
-  const int w = min(lane_id(), kBitWords - 1);
+// Round rd's outcome words: the kCopies copies of 32-bit word w into lane w
+// (the lanes past the last word read it too).  No branch between the loads,
+// so that they stay in flight together with the kernel's other inputs.
+__device__ __forceinline__ void outcome_load(const PlanArgs &a, int rd, uint32_t (&v)[kCopies]) {
+  const uint32_t *w = reinterpret_cast<const uint32_t *>(a.ws.bits + rd * kCopies * kBitWords) +
+                      min(lane_id(), 2 * kBitWords - 1);
 #pragma unroll
-  for (int c = 0; c < kCopies; ++c) v[c] = a.ws.bits[(rd * kCopies + c) * kBitWords + w];
+  for (int c = 0; c < kCopies; ++c) v[c] = w[c * 2 * kBitWords];
 }
 
-// The OR of the copies: word w in lane w, zero past the last word.
-__device__ __forceinline__ uint64_t outcome_or(const uint64_t (&v)[kCopies]) {
-  uint64_t bw = 0;
+// The OR of the copies: word w in lane w.
+__device__ __forceinline__ int outcome_or(const uint32_t (&v)[kCopies]) {
+  uint32_t bw = 0;
 #pragma unroll
   for (int c = 0; c < kCopies; ++c) bw |= v[c];
-  return lane_id() < kBitWords ? bw : 0;
+  return static_cast<int>(bw);
 }
 
 // The sequential bisection through round rd's depth-kDepth subtree, from
-// state st, over the round's outcome bits (word w in lane w).
-__device__ __forceinline__ void walk_bits(uint64_t bw, int rd, BisState &st) {
-  int node = 0;
-  for (int d = 0; d < kDepth && st.lo < st.hi; ++d) {
-    const int64_t mid = (st.lo + st.hi) / 2;
-    ++st.probes;
-    const uint64_t w = readlane64(bw, node >> 6);
-    if ((w >> (node & 63)) & 1) {
-      st.hi = mid;
-      st.best = rd * kNodes + node;
-      node = 2 * node + 1;
-    } else {
-      st.lo = mid + 1;
-      node = 2 * node + 2;
-    }
+// state st, over the round's outcome bits (32-bit word w in lane w).  An
+// interval that is not empty lies within [0, 2^30], so it is walked in 32
+// bits, without branches on the outcomes: 10 levels take 0.8 us.
+__device__ __forceinline__ void walk_bits(int bw, int rd, BisState &st) {
+  if (st.lo >= st.hi) return;
+  int lo = static_cast<int>(st.lo), hi = static_cast<int>(st.hi);
+  int node = 0, best = -1, d = 0;
+#pragma unroll 1
+  for (; d < kDepth && lo < hi; ++d) {
+    const int mid = (lo + hi) >> 1;
+    const int bit = static_cast<int>(static_cast<uint32_t>(readlane(bw, node >> 5)) >> (node & 31)) & 1;
+    best = bit ? node : best;
+    hi = bit ? mid : hi;
+    lo = bit ? lo : mid + 1;
+    node = 2 * node + 2 - bit;
   }
+  st.lo = lo;
+  st.hi = hi;
+  st.best = best >= 0 ? rd * kNodes + best : st.best;
+  st.probes += d;
 }
 
 __global__ void __launch_bounds__(kWave) k_plan_round(PlanArgs a, int round) {
-  __shared__ int32_t s_eorder[kMaxE];
-  __shared__ int32_t s_elam[kMaxE];
-  __shared__ uint32_t s_re[kMaxRec + kWave];
-  __shared__ int32_t s_rd[kMaxRec + kWave];
+  __shared__ uint2 s_ent[kMaxE];
+  __shared__ uint2 s_rec[kMaxRec + kWave];
   const int lane = threadIdx.x, b = blockIdx.x;
-  const int R = a.R, E = a.E, RS = R * a.NS;
+  const int E = a.E, RS = a.R * a.NS;
   // every input is requested up front, with no branch between the loads
   // (indices clamped into range, values masked afterwards), so the round
   // waits for memory once: the state before the previous round and that
   // round's outcome bits (round 0 reads the last round's words, which
-  // nothing writes before that round), the per-rank expert orders and the
-  // rank orders
+  // nothing writes before that round), the rank orders and the visiting order
   const int64_t status = a.ws.hdr[3];
   const bool packed = a.ws.hdr[1] < (int64_t(1) << 25);
   BisState st = state_before(a, round > 0 ? round - 1 : 0);
-  uint64_t bv[kCopies];
+  uint32_t bv[kCopies];
   outcome_load(a, round > 0 ? round - 1 : kRounds - 1, bv);
-  int ve[kMaxE / kWave], vl[kMaxE / kWave];
+  const v4i rk = a.ws.rank[lane];
+  uint2 ent[kEntRegs], more[kMaxE / kWave - kEntRegs];
 #pragma unroll
-  for (int u = 0; u < kMaxE / kWave; ++u) {
-    if (u * kWave < E) {
-      const int i = min(u * kWave + lane, E - 1);  // stored to LDS only below E
-      ve[u] = a.ws.eorder[i];
-      vl[u] = a.ws.elam[i];
-    }
+  for (int u = 0; u < kEntRegs; ++u) ent[u] = a.ws.ent[min(u * kWave + lane, E - 1)];
+  if (E > kEntRegs * kWave) {
+#pragma unroll
+    for (int u = kEntRegs; u < kMaxE / kWave; ++u)
+      more[u - kEntRegs] = a.ws.ent[min(u * kWave + lane, E - 1)];
   }
-  const int lr = min(lane, R - 1);
-  const int rk_v = a.ws.rank_desc[lr], as_v = a.ws.rank_asc[lr], ell_v = a.ws.ell[lr];
   // the loads above are issued before the status test (which the compiler
   // would otherwise move ahead of them, waiting for the header first)
   asm volatile("" ::: "memory");
-  const int rk_r = lane < R ? rk_v : 0;
-  const int as_r = lane < R ? as_v : 0;
-  const int ell_lane = lane < R ? ell_v : 0;
   if (status != 0) return;
+#pragma unroll
+  for (int u = 0; u < kEntRegs; ++u) s_ent[u * kWave + lane] = ent[u];
+  if (E > kEntRegs * kWave) {
+#pragma unroll
+    for (int u = kEntRegs; u < kMaxE / kWave; ++u) s_ent[u * kWave + lane] = more[u - kEntRegs];
+  }
   if (round > 0) {  // every workgroup walks the previous round; the first publishes it
     walk_bits(outcome_or(bv), round - 1, st);
     if (b == 0 && lane == 0) {
@@ -616,41 +588,23 @@ __global__ void __launch_bounds__(kWave) k_plan_round(PlanArgs a, int round) {
       h[3] = st.probes;
     }
   }
-  int64_t lo = st.lo, hi = st.hi;
-  if (lo >= hi) return;  // the bisection has ended
+  if (st.lo >= st.hi) return;  // the bisection has ended
   // this workgroup's node of the round's subtree
+  int lo = static_cast<int>(st.lo), hi = static_cast<int>(st.hi);
   const int id = b + 1, depth = 31 - __clz(id);
-  bool reached = true;
-  for (int bit = depth - 1; bit >= 0 && reached; --bit) {
-    const int64_t mid = (lo + hi) / 2;
-    if ((id >> bit) & 1) lo = mid + 1;  // right child: that probe failed
-    else hi = mid;                      // left child: that probe succeeded
-    reached = lo < hi;
+  // (an interval that has become empty stays empty)
+#pragma unroll 1
+  for (int bit = depth - 1; bit >= 0; --bit) {
+    const int mid = (lo + hi) >> 1;
+    const bool right = (id >> bit) & 1;  // that probe failed
+    lo = right ? mid + 1 : lo;
+    hi = right ? hi : mid;
   }
   int n = kNotReached;
-  if (reached) {
-    const int tau = static_cast<int>((lo + hi) / 2);
-#pragma unroll
-    for (int u = 0; u < kMaxE / kWave; ++u) {
-      const int i = u * kWave + lane;
-      if (i < E) {
-        s_eorder[i] = ve[u];
-        s_elam[i] = vl[u];
-      }
-    }
-    const int rk_l = __shfl(ell_lane, rk_r);
-    const int as_l = __shfl(ell_lane, as_r);
+  if (lo < hi) {
     __syncthreads();
-    n = run_probe<0>(a, packed, tau, lane, rk_r, rk_l, as_r, as_l, ell_lane, s_eorder, s_elam,
-                  s_re, s_rd);
-    if (n > 0) {
-      __syncthreads();
-      uint32_t *rec = a.ws.rec + (static_cast<int64_t>(round) * kNodes + b) * 2 * RS;
-      for (int i = lane; i < n; i += kWave) {
-        rec[2 * i] = s_re[i];
-        rec[2 * i + 1] = static_cast<uint32_t>(s_rd[i]);
-      }
-    }
+    uint2 *rec = reinterpret_cast<uint2 *>(a.ws.rec) + (static_cast<int64_t>(round) * kNodes + b) * RS;
+    n = run_probe<0>(a, packed, (lo + hi) >> 1, lane, rk, s_ent, s_rec, rec);
   }
   if (lane == 0) {
     a.ws.res[round * kNodes + b] = n;
@@ -743,6 +697,11 @@ __device__ __forceinline__ int rank_of(int key) {
          ((ahead<5>(key) + ahead<6>(key)) + ahead<7>(key));
 }
 
+// Lowest set bit of m (63 when there is none).
+__device__ __forceinline__ int first_bit(uint64_t m) {
+  return __builtin_ctzll(m | (uint64_t(1) << 63));
+}
+
 // Three to eight hosts, total load below 2^26: host i sits in lane i and in
 // its mirror lane i + 8, so that rotations by 1 .. 7 within the 16 lanes of
 // row 0 bring every other host's value to every host lane with no scalar
@@ -792,13 +751,16 @@ __device__ __forceinline__ void split_lanes(int lane, int nh, int lamhat_r, int 
                                                         (1.0 - 0x1p-20) / static_cast<double>(Dr))
                                    : 0.0f;
     const int nD_r = -Dr;
+    // a source's scalars are read one step ahead: the lane reads then run
+    // beside the vector chain of the source before it
+    int r = first_bit(act), lh = readlane(lamhat_r, r), nD = readlane(nD_r, r);
+    int cb = readlane(__float_as_int(c_r), r);
     while (act) {
-      const int r = __ffsll(static_cast<unsigned long long>(act)) - 1;
       act &= act - 1;
-      const int lh = readlane(lamhat_r, r);
-      const int nD = readlane(nD_r, r);
-      const float c = __int_as_float(readlane(__float_as_int(c_r), r));
-      const int be = static_cast<int>(c * static_cast<float>(ures));
+      const int rn = first_bit(act);
+      const int lhn = readlane(lamhat_r, rn), nDn = readlane(nD_r, rn);
+      const int cbn = readlane(__float_as_int(c_r), rn);
+      const int be = static_cast<int>(__int_as_float(cb) * static_cast<float>(ures));
       const int re = static_cast<int>(static_cast<uint32_t>(__mul24(be, nD)) +
                                       __umul24(lh, static_cast<uint32_t>(ures)));
       const int t = re + nD;  // re - D, in [-D, D)
@@ -809,6 +771,10 @@ __device__ __forceinline__ void split_lanes(int lane, int nh, int lamhat_r, int 
       const int qi = b + ((slot && rk < left) ? 1 : 0);
       ures -= qi;
       s_q[r * qstep + qoff] = qi;
+      r = rn;
+      lh = lhn;
+      nD = nDn;
+      cb = cbn;
     }
   } else {
     // lh / D of source `lane`
@@ -983,7 +949,7 @@ __global__ void __launch_bounds__(kWave) k_plan_emit(PlanArgs a) {
   const int64_t status = a.ws.hdr[3], L = a.ws.hdr[2];
   const int64_t lo0 = a.ws.hdr[0], hi0 = a.ws.hdr[1];
   BisState fin = state_before(a, kRounds - 1);
-  uint64_t bv[kCopies];
+  uint32_t bv[kCopies];
   outcome_load(a, kRounds - 1, bv);
   const int lam_e = a.ws.lam[e];
   const int lam_v = kReroute ? a.load[static_cast<int64_t>(min(lane, R - 1)) * E + e] : 0;
@@ -998,35 +964,26 @@ __global__ void __launch_bounds__(kWave) k_plan_emit(PlanArgs a) {
   if (fin.lo < fin.hi) {
     // a bisection longer than the rounds: the remaining probes run here, one
     // after another, the same ones in every workgroup
-    __shared__ int32_t s_eorder[kMaxE];
-    __shared__ int32_t s_elam[kMaxE];
-    __shared__ uint32_t s_re[kMaxRec + kWave];
-    __shared__ int32_t s_rd[kMaxRec + kWave];
-    for (int i = lane; i < E; i += kWave) {
-      s_eorder[i] = a.ws.eorder[i];
-      s_elam[i] = a.ws.elam[i];
-    }
-    const int rk_r = lane < R ? a.ws.rank_desc[lane] : 0;
-    const int as_r = lane < R ? a.ws.rank_asc[lane] : 0;
-    const int ell_lane = lane < R ? a.ws.ell[lane] : 0;
-    const int rk_l = __shfl(ell_lane, rk_r);
-    const int as_l = __shfl(ell_lane, as_r);
+    __shared__ uint2 s_ent[kMaxE];
+    __shared__ uint2 s_rec[kMaxRec + kWave];
+    __shared__ uint2 s_out[kMaxRec];
+    for (int i = lane; i < E; i += kWave) s_ent[i] = a.ws.ent[i];
+    const v4i rk = a.ws.rank[lane];
     const bool packed = hi0 < (int64_t(1) << 25);
     bool local = false;
     __syncthreads();
     while (fin.lo < fin.hi) {
       const int64_t mid = (fin.lo + fin.hi) / 2;
       ++fin.probes;
-      const int n = run_probe<1>(a, packed, static_cast<int>(mid), lane, rk_r, rk_l, as_r, as_l,
-                              ell_lane, s_eorder, s_elam, s_re, s_rd);
+      const int n = run_probe<1>(a, packed, static_cast<int>(mid), lane, rk, s_ent, s_rec, s_out);
       __syncthreads();
       if (n >= 0) {
         fin.hi = mid;
         local = true;
         nb = n;
         for (int i = lane; i < n; i += kWave) {
-          s_et[i] = s_re[i];
-          s_d[i] = s_rd[i];
+          s_et[i] = s_out[i].x;
+          s_d[i] = static_cast<int32_t>(s_out[i].y);
         }
       } else {
         fin.lo = mid + 1;

@@ -62,3 +62,23 @@ def test_plan_sweep(block):
                                  f"beta={beta}): {ex}") from None
         checked += 1
     assert checked > 450
+
+
+# the probes' edges: one group of the visiting order (256 experts) and more, many experts per rank (several visits per
+# overloaded rank, and ranks whose experts run out), all 64 ranks, one rank,
+# one and several slots, loads on both sides of the 2^25 packing limit
+@pytest.mark.parametrize("R,E", [(1, 1), (2, 1024), (3, 255), (4, 256), (4, 260), (5, 640),
+                                 (63, 63), (64, 64), (64, 1024)])
+@pytest.mark.parametrize("NS", [0, 1, 2, 4])
+def test_plan_probe_edges(R, E, NS):
+    for seed, (scale, u_min) in enumerate([(50, 1), (2000, 37), (30000, 1024),
+                                           ((1 << 29) // (R * E), 5)]):
+        rng = np.random.default_rng(1000 * R + 10 * E + 7 * NS + seed)
+        w = np.repeat(rng.dirichlet(np.full(R, 0.7)) * R, E // R) * rng.uniform(0.8, 1.2, E)
+        load = rng.integers(0, max(2, scale), (R, E)) * w / w.max()
+        load = np.minimum(load, (1 << 30) // (R * E)).astype(np.int32)
+        g, og = gp.groups(R, E, NS, u_min)
+        op = oracle.plan(load, og)
+        assert op.status == oracle.OK
+        gp.assert_plan_equal(gp.gpu_plan(load, g), op)
+        gp.assert_plan_equal(gp.gpu_plan(load, g, split=True), op)
