@@ -372,73 +372,79 @@ constexpr int kScWaves = kScThreads / kWave;
 // walks tokens t, t + 2048, ...  Measured against one wave per token and
 // against 256 to 1024 workgroups on the DeepSeek-V3-shaped layer.
 constexpr int kScGrid = 512;
+constexpr int64_t kScSplit = 768;  // tokens below which rows are cut
+constexpr int64_t kScFill = 2048;  // units that fill the resident waves
 // dword 3 of a raw buffer resource (32-bit data format) and the store cache
 // policy: sc1 streams the rows out at the device scope.  Buffer stores with
 // sc1 measured 3-4 % faster than plain or non-temporal global stores.
 constexpr uint32_t kRawBufferWord3 = 0x00020000u;
 constexpr int kStoreSc1 = 16;
 
-// Stores chunk-lane values of one token to its k destination rows, one 1 KiB
-// chunk (64 lanes x 16 B) to every row before the next chunk.  Each row gets
-// its own buffer resource (base = the row, size = the row), so offsets stay
-// 32-bit and anything past the row is dropped by the hardware.
+// Stores chunk-lane values of one token (chunks c0 .. c0 + 64 U - 1) to its k
+// destination rows, one 1 KiB chunk (64 lanes x 16 B) to every row before the
+// next chunk.  Each row gets its own buffer resource (base = the row, size =
+// the row), so offsets stay 32-bit and anything past the row is dropped by
+// the hardware.
 template <int U>
 __device__ __forceinline__ void store_rows(const v4u (&v)[U], int rows, int k, int64_t V,
-                                           int32_t nch, int lane, v4u *send) {
+                                           int32_t nch, int c0, int lane, v4u *send) {
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const int cc = u * kWave + lane;
+    const int cc = c0 + u * kWave + lane;
     if (cc < nch) {
       for (int kk = 0; kk < k; ++kk) {
         const int row = readlane(rows, kk);
         if (row >= 0 && row < V) {
           const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-              send + static_cast<int64_t>(row) * nch, 0, nch * 16, kRawBufferWord3);
-          __builtin_amdgcn_raw_buffer_store_b128(v[u], r, cc * 16, 0, kStoreSc1);
+              send + static_cast<int64_t>(row) * nch, 0, static_cast<uint32_t>(nch) * 16u,
+              kRawBufferWord3);
+          __builtin_amdgcn_raw_buffer_store_b128(v[u], r, static_cast<uint32_t>(cc) * 16u, 0,
+                                                 kStoreSc1);
         }
       }
     }
   }
 }
 
-// Rows of up to 64 * U chunks (H <= 8192): persistent waves, each holding
-// one token row in registers while the next token's row is being loaded.
-template <int U>
+// Rows of up to 64 * U chunks (H <= 8192), one unit each, or (kSplit) rows cut
+// into `pieces` units of 64 * U chunks: persistent waves, each holding one
+// unit in registers while the next one is being loaded.
+template <int U, bool kSplit>
 __global__ void __launch_bounds__(kScThreads)
-k_scatter(const v4u *__restrict__ x, int64_t T, int32_t k, int32_t nch,
+k_scatter(const v4u *__restrict__ x, int64_t T, int32_t k, int32_t nch, int32_t pieces,
           const int32_t *__restrict__ row_of_slot, const int64_t *n_routed,
           v4u *__restrict__ send) {
   const int lane = lane_id();
-  const int64_t V = T * k;
+  const int64_t V = T * k, n = kSplit ? T * pieces : T;
   const int64_t nw = static_cast<int64_t>(gridDim.x) * kScWaves;
   const int64_t gw = static_cast<int64_t>(blockIdx.x) * kScWaves + threadIdx.x / kWave;
-  int64_t t = gw;
-  if (t < T) {
-    v4u v[U];
+  const auto fetch = [&](int64_t unit, v4u(&v)[U], int &rows, int &c0) {
+    const int64_t t = kSplit ? unit / pieces : unit;
+    c0 = kSplit ? static_cast<int>(unit - t * pieces) * (kWave * U) : 0;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int cc = u * kWave + lane;
+      const int cc = c0 + u * kWave + lane;
       if (cc < nch) v[u] = __builtin_nontemporal_load(x + t * nch + cc);
     }
-    int rows = lane < k ? row_of_slot[t * k + lane] : -1;
+    rows = lane < k ? row_of_slot[t * k + lane] : -1;
+  };
+  int64_t unit = gw;
+  if (unit < n) {
+    v4u v[U];
+    int rows, c0;
+    fetch(unit, v, rows, c0);
     for (;;) {
-      const int64_t tn = t + nw;
+      const int64_t un = unit + nw;
       v4u w[U];
-      int rn = -1;
-      if (tn < T) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int cc = u * kWave + lane;
-          if (cc < nch) w[u] = __builtin_nontemporal_load(x + tn * nch + cc);
-        }
-        rn = lane < k ? row_of_slot[tn * k + lane] : -1;
-      }
-      store_rows<U>(v, rows, k, V, nch, lane, send);
-      if (tn >= T) break;
+      int rn = -1, cn = 0;
+      if (un < n) fetch(un, w, rn, cn);
+      store_rows<U>(v, rows, k, V, nch, c0, lane, send);
+      if (un >= n) break;
 #pragma unroll
       for (int u = 0; u < U; ++u) v[u] = w[u];
       rows = rn;
-      t = tn;
+      c0 = cn;
+      unit = un;
     }
   }
   // rows after the routed ones (masked slots) are zero-filled
@@ -451,45 +457,13 @@ k_scatter(const v4u *__restrict__ x, int64_t T, int32_t k, int32_t nch,
   }
 }
 
-// Longer rows: one wave per token, the row in passes of 1024 chunks.
-__global__ void __launch_bounds__(kScThreads)
-k_scatter_wide(const v4u *__restrict__ x, int64_t T, int32_t k, int32_t nch,
-               const int32_t *__restrict__ row_of_slot, const int64_t *n_routed,
-               v4u *__restrict__ send) {
-  constexpr int U = 16;
-  const int lane = lane_id();
-  const int64_t V = T * k;
-  const int64_t gw = static_cast<int64_t>(blockIdx.x) * kScWaves + threadIdx.x / kWave;
-  const int64_t nw = static_cast<int64_t>(gridDim.x) * kScWaves;
-  for (int64_t t = gw; t < T; t += nw) {
-    const int rows = lane < k ? row_of_slot[t * k + lane] : -1;
-    const v4u *src = x + t * nch;
-    for (int c0 = 0; c0 < nch; c0 += U * kWave) {
-      v4u v[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int cc = c0 + u * kWave + lane;
-        if (cc < nch) v[u] = __builtin_nontemporal_load(src + cc);
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int cc = c0 + u * kWave + lane;
-        if (cc < nch) {
-          for (int kk = 0; kk < k; ++kk) {
-            const int row = readlane(rows, kk);
-            if (row >= 0 && row < V) send[static_cast<int64_t>(row) * nch + cc] = v[u];
-          }
-        }
-      }
-    }
-  }
-  // a routed count outside [0, V] (not a layout of these slots) fills no row
-  const int64_t nr = *n_routed;
-  if (nr >= 0 && nr < V) {
-    const v4u z = v4u{0u, 0u, 0u, 0u};
-    for (int64_t row = nr + gw; row < V; row += nw)
-      for (int cc = lane; cc < nch; cc += kWave) send[row * nch + cc] = z;
-  }
+template <int U, bool kSplit>
+static void start_scatter(const v4u *x, int64_t T, int32_t k, int32_t nch, const int32_t *row_of_slot,
+                          const int64_t *n_routed, v4u *send, hipStream_t stream) {
+  const int32_t pieces = kSplit ? (nch + U * kWave - 1) / (U * kWave) : 1;
+  const int64_t need = (T * pieces + kScWaves - 1) / kScWaves;
+  hipLaunchKernelGGL((k_scatter<U, kSplit>), dim3(static_cast<unsigned>(need < kScGrid ? need : kScGrid)),
+                     dim3(kScThreads), 0, stream, x, T, k, nch, pieces, row_of_slot, n_routed, send);
 }
 
 hipError_t launch_dispatch_scatter(const uint16_t *x, int64_t T, int32_t k,
@@ -497,26 +471,37 @@ hipError_t launch_dispatch_scatter(const uint16_t *x, int64_t T, int32_t k,
                                    const int64_t *n_routed, uint16_t *send,
                                    hipStream_t stream) {
   const int32_t nch = H / 8;
-  const int64_t need = (T + kScWaves - 1) / kScWaves;
-  const dim3 grid(static_cast<unsigned>(need < kScGrid ? (need > 0 ? need : 1) : kScGrid));
-  const int per_lane = (nch + kWave - 1) / kWave;
+  const int per_lane = nch / kWave + (nch % kWave != 0);
   const v4u *xs = reinterpret_cast<const v4u *>(x);
   v4u *sd = reinterpret_cast<v4u *>(send);
-  const dim3 blk(kScThreads);
-  if (per_lane <= 1)
-    hipLaunchKernelGGL(k_scatter<1>, grid, blk, 0, stream, xs, T, k, nch, row_of_slot, n_routed, sd);
-  else if (per_lane <= 2)
-    hipLaunchKernelGGL(k_scatter<2>, grid, blk, 0, stream, xs, T, k, nch, row_of_slot, n_routed, sd);
-  else if (per_lane <= 4)
-    hipLaunchKernelGGL(k_scatter<4>, grid, blk, 0, stream, xs, T, k, nch, row_of_slot, n_routed, sd);
-  else if (per_lane <= 8)
-    hipLaunchKernelGGL(k_scatter<8>, grid, blk, 0, stream, xs, T, k, nch, row_of_slot, n_routed, sd);
-  else if (per_lane <= 14)
-    hipLaunchKernelGGL(k_scatter<14>, grid, blk, 0, stream, xs, T, k, nch, row_of_slot, n_routed, sd);
-  else if (per_lane <= 16)
-    hipLaunchKernelGGL(k_scatter<16>, grid, blk, 0, stream, xs, T, k, nch, row_of_slot, n_routed, sd);
-  else
-    hipLaunchKernelGGL(k_scatter_wide, grid, blk, 0, stream, xs, T, k, nch, row_of_slot, n_routed, sd);
+  const auto start = [&](auto f) { f(xs, T, k, nch, row_of_slot, n_routed, sd, stream); };
+  // Whole rows per wave keep the stores of a row together; they are cut where
+  // that leaves waves idle or where a row does not fit the registers.  Below
+  // kScSplit tokens: the widest units that still make kScFill of them.
+  // Layout and scatter in whole rows / cut, k = 8: 64 tokens of H = 4096
+  // 16.6 / 10.7 us, 256 tokens 17.9 / 13.2, 512 tokens of H = 7168 23.7 / 20.1,
+  // but 1000 of them 31.8 / 32.4 and 1500 of H = 4096 26.8 / 27.4 (units of 256
+  // chunks).  H = 12288: 300 tokens 31.6 / 19.6 us, 4000 tokens 188.6 / 186.4
+  // against one wave per token walking the row in passes.
+  const auto fills = [&](int u) { return T * ((per_lane + u - 1) / u) >= kScFill; };
+  if (per_lane > 16 || (per_lane > 1 && T < kScSplit)) {
+    if (per_lane > 8 && fills(8)) start(start_scatter<8, true>);
+    else if (per_lane > 4 && fills(4)) start(start_scatter<4, true>);
+    else if (per_lane > 2 && fills(2)) start(start_scatter<2, true>);
+    else start(start_scatter<1, true>);
+  } else if (per_lane <= 1) {
+    start(start_scatter<1, false>);
+  } else if (per_lane <= 2) {
+    start(start_scatter<2, false>);
+  } else if (per_lane <= 4) {
+    start(start_scatter<4, false>);
+  } else if (per_lane <= 8) {
+    start(start_scatter<8, false>);
+  } else if (per_lane <= 14) {
+    start(start_scatter<14, false>);
+  } else {
+    start(start_scatter<16, false>);
+  }
   return hipGetLastError();
 }
 

@@ -18,6 +18,7 @@ pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
     import gpu_path as gp
+    import paper_2606_04101_amd as uep
 
 
 def sweep_routing(seed):
@@ -126,3 +127,24 @@ def test_extension_sweep(block):
             raise AssertionError(f"{where}: {ex}") from None
         checked += 1
     assert checked > 120
+
+
+# rows in one unit and cut into units of 1, 2, 4 and 8 chunks per lane (few
+# tokens, wide rows), widths around the units' edges, tokens around the rule
+@pytest.mark.parametrize("T,k", [(1, 1), (5, 3), (300, 2), (767, 2), (768, 2), (1030, 1)])
+@pytest.mark.parametrize("H", [8, 512, 520, 1032, 4096, 4104, 7168, 8192, 8200, 12296])
+def test_scatter_units(T, k, H):
+    rng = np.random.default_rng(T * 10 + H)
+    V = T * k
+    x = rng.integers(0, 1 << 16, (T, H)).astype(np.uint16)
+    routed = rng.random(V) >= 0.2
+    ros = np.full(V, -1, np.int32)
+    nr = int(routed.sum())
+    ros[routed] = rng.permutation(nr)
+    send = torch.full((V, H), 0x5A5A, dtype=torch.int16, device=gp.DEV)
+    uep.ultraep_dispatch_scatter(gp.dev_u16(x), T, k, H, gp.dev_i32(ros),
+                                 torch.tensor([nr], dtype=torch.int64, device=gp.DEV), send)
+    torch.cuda.synchronize()
+    ref = np.zeros((V, H), np.uint16)
+    ref[ros[routed]] = x[np.arange(V)[routed] // k]
+    assert np.array_equal(gp.host_u16(send), ref)
