@@ -5,7 +5,11 @@ Every function has the name of the C entry point it calls and only marshals
 arguments: torch tensors supply device memory, torch's current HIP stream is
 used unless another one is given, and every step runs in the library's HIP
 kernels.  Before a call it checks that every tensor is large enough for the
-shapes given, so a kernel never runs past a caller's buffer.  A missing library raises immediately; there is no fallback path.
+shapes given, so a kernel never runs past a caller's buffer.  A call whose
+arguments pass the checks goes through ``_native.so`` (``csrc/binding.cpp``),
+which makes them in C++; one that it does not take (None is returned) is
+checked, and refused or made, by the ctypes code below.  A missing library
+raises immediately; there is no fallback path.
 
 Reference: "UltraEP: Unleash MoE Training and Inference on Rack-Scale Nodes
 with Near-Optimal Load Balancing", arXiv 2606.04101 (Algorithm 1, Sec. 5-6).
@@ -66,6 +70,7 @@ PLAN_FIELDS = ("slot_expert", "quota", "host_ptr", "host_rank", "host_pslot",
                "reroute", "stats")
 
 _lib = None
+_native = None
 _P = ctypes.c_void_p
 
 
@@ -113,6 +118,26 @@ def lib():
             getattr(L, f).restype = ctypes.c_int
         _lib = L
     return _lib
+
+
+def _load_native():
+    """The native half of the binding, bound to the library's entry points."""
+    global _native
+    path = os.path.join(_HERE, "_native.so")
+    if not os.path.exists(path):
+        raise RuntimeError(f"{path} is not built; run __graft_entry__.build() first")
+    import importlib
+
+    import torch  # noqa: F401  (the module links against torch's libraries)
+    L = lib()
+    m = importlib.import_module("._native", __name__)
+    m.bind({f"ultraep_{n}": ctypes.cast(getattr(L, f"ultraep_{n}"), _P).value
+            for n in ("count", "plan", "plan_noalloc", "plan_replicate", "plan_reroute",
+                      "dispatch", "dispatch_layout", "dispatch_scatter", "pack_replicas",
+                      "reroute_and_pack", "relay_plan", "pack_relay", "combine",
+                      "grad_reduce")}, Group, Plan, PlanBuf)
+    _native = m
+    return m
 
 
 def ultraep_strerror(code: int) -> str:
@@ -179,6 +204,9 @@ class Plan:
 
 
 def ultraep_count(topk, T, k, E, n_groups, counts, status, stream=None):
+    rc = (_native or _load_native()).count(topk, T, k, E, n_groups, counts, status, stream)
+    if rc is not None:
+        return rc if rc == ULTRAEP_OK else _check(rc, "ultraep_count")
     _need(topk, n_groups * T * k, 4, "topk")
     _need(counts, n_groups * E, 4, "counts")
     _need(status, 1, 4, "status")
@@ -193,6 +221,9 @@ def ultraep_plan_ws_bytes(g: Group) -> int:
 
 def ultraep_plan(load, g: Group, plan: Plan, ws=None, stream=None):
     """ws: device workspace (defaults to the one the Plan object holds)."""
+    rc = (_native or _load_native()).plan(load, g, plan, ws, stream)
+    if rc is not None:
+        return rc if rc == ULTRAEP_OK else _check(rc, "ultraep_plan")
     ws = plan.ws if ws is None else ws
     _need(load, g.R * g.E, 4, "load")
     return _check(lib().ultraep_plan(_ptr(load), ctypes.byref(g),
@@ -204,6 +235,9 @@ def ultraep_plan(load, g: Group, plan: Plan, ws=None, stream=None):
 def ultraep_plan_noalloc(load, g: Group, plan: Plan, stream=None):
     """ultraep_plan with the library's fixed per-device workspace (plan.ws is
     not used); calls on one device must not overlap in time."""
+    rc = (_native or _load_native()).plan_noalloc(load, g, plan, stream)
+    if rc is not None:
+        return rc if rc == ULTRAEP_OK else _check(rc, "ultraep_plan_noalloc")
     _need(load, g.R * g.E, 4, "load")
     return _check(lib().ultraep_plan_noalloc(_ptr(load), ctypes.byref(g),
                                              ctypes.byref(plan.c), _stream(stream)),
@@ -211,6 +245,9 @@ def ultraep_plan_noalloc(load, g: Group, plan: Plan, stream=None):
 
 
 def ultraep_plan_replicate(load, g: Group, plan: Plan, ws=None, stream=None):
+    rc = (_native or _load_native()).plan_replicate(load, g, plan, ws, stream)
+    if rc is not None:
+        return rc if rc == ULTRAEP_OK else _check(rc, "ultraep_plan_replicate")
     ws = plan.ws if ws is None else ws
     _need(load, g.R * g.E, 4, "load")
     return _check(lib().ultraep_plan_replicate(
@@ -219,6 +256,9 @@ def ultraep_plan_replicate(load, g: Group, plan: Plan, ws=None, stream=None):
 
 
 def ultraep_plan_reroute(load, g: Group, plan: Plan, stream=None):
+    rc = (_native or _load_native()).plan_reroute(load, g, plan, stream)
+    if rc is not None:
+        return rc if rc == ULTRAEP_OK else _check(rc, "ultraep_plan_reroute")
     _need(load, g.R * g.E, 4, "load")
     return _check(lib().ultraep_plan_reroute(
         _ptr(load), ctypes.byref(g), ctypes.byref(plan.c), _stream(stream)),
@@ -238,6 +278,10 @@ def _layout_need(topk, T, k, g, row_of_slot, block_off, status):
 
 def ultraep_dispatch(x, topk, T, k, H, rank, g: Group, plan: Plan, send,
                      row_of_slot, block_off, ws, status, stream=None):
+    rc = (_native or _load_native()).dispatch(x, topk, T, k, H, rank, g, plan, send, row_of_slot,
+                                             block_off, ws, status, stream)
+    if rc is not None:
+        return rc if rc == ULTRAEP_OK else _check(rc, "ultraep_dispatch")
     _need(x, T * H, 2, "x")
     _need(send, T * k * H, 2, "send")
     _layout_need(topk, T, k, g, row_of_slot, block_off, status)
@@ -250,6 +294,10 @@ def ultraep_dispatch(x, topk, T, k, H, rank, g: Group, plan: Plan, send,
 
 def ultraep_dispatch_layout(topk, T, k, rank, g: Group, plan: Plan,
                             row_of_slot, block_off, ws, status, stream=None):
+    rc = (_native or _load_native()).dispatch_layout(topk, T, k, rank, g, plan, row_of_slot,
+                                                    block_off, ws, status, stream)
+    if rc is not None:
+        return rc if rc == ULTRAEP_OK else _check(rc, "ultraep_dispatch_layout")
     _layout_need(topk, T, k, g, row_of_slot, block_off, status)
     return _check(lib().ultraep_dispatch_layout(
         _ptr(topk), T, k, rank, ctypes.byref(g), ctypes.byref(plan.c),
@@ -261,6 +309,10 @@ def ultraep_dispatch_layout(topk, T, k, rank, g: Group, plan: Plan,
 def ultraep_dispatch_scatter(x, T, k, H, row_of_slot, n_routed, send,
                              stream=None):
     """n_routed: a one-element int64 device tensor (e.g. block_off[-1:])."""
+    rc = (_native or _load_native()).dispatch_scatter(x, T, k, H, row_of_slot, n_routed, send,
+                                                     stream)
+    if rc is not None:
+        return rc if rc == ULTRAEP_OK else _check(rc, "ultraep_dispatch_scatter")
     _need(x, T * H, 2, "x")
     _need(row_of_slot, T * k, 4, "row_of_slot")
     _need(n_routed, 1 if T > 0 else 0, 8, "n_routed")
@@ -279,6 +331,10 @@ def _pack_need(w_main, W, g, staging, cap, dest_off, status):
 
 def ultraep_pack_replicas(w_main, W, rank, g: Group, plan: Plan, staging, cap,
                           dest_off, status, stream=None):
+    rc = (_native or _load_native()).pack_replicas(w_main, W, rank, g, plan, staging, cap,
+                                                  dest_off, status, stream)
+    if rc is not None:
+        return rc if rc == ULTRAEP_OK else _check(rc, "ultraep_pack_replicas")
     _pack_need(w_main, W, g, staging, cap, dest_off, status)
     return _check(lib().ultraep_pack_replicas(
         _ptr(w_main), W, rank, ctypes.byref(g), ctypes.byref(plan.c),
@@ -288,6 +344,10 @@ def ultraep_pack_replicas(w_main, W, rank, g: Group, plan: Plan, staging, cap,
 
 def ultraep_reroute_and_pack(load, g: Group, plan: Plan, w_main, W, rank, staging,
                              cap, dest_off, status, stream=None):
+    rc = (_native or _load_native()).reroute_and_pack(load, g, plan, w_main, W, rank, staging,
+                                                     cap, dest_off, status, stream)
+    if rc is not None:
+        return rc if rc == ULTRAEP_OK else _check(rc, "ultraep_reroute_and_pack")
     _need(load, g.R * g.E, 4, "load")
     _pack_need(w_main, W, g, staging, cap, dest_off, status)
     return _check(lib().ultraep_reroute_and_pack(
@@ -298,6 +358,10 @@ def ultraep_reroute_and_pack(load, g: Group, plan: Plan, w_main, W, rank, stagin
 
 def ultraep_relay_plan(g: Group, plan: Plan, threshold, slot_src, send_vol,
                        relay_stats, status, stream=None):
+    rc = (_native or _load_native()).relay_plan(g, plan, threshold, slot_src, send_vol,
+                                               relay_stats, status, stream)
+    if rc is not None:
+        return rc if rc == ULTRAEP_OK else _check(rc, "ultraep_relay_plan")
     _need(slot_src, g.R * g.n_slot, 4, "slot_src")
     _need(send_vol, g.R, 4, "send_vol")
     _need(relay_stats, 4, 8, "relay_stats")
@@ -310,6 +374,10 @@ def ultraep_relay_plan(g: Group, plan: Plan, threshold, slot_src, send_vol,
 
 def ultraep_pack_relay(w_main, relay_src, W, rank, g: Group, plan: Plan, slot_src,
                        staging, cap, dest_off, status, stream=None):
+    rc = (_native or _load_native()).pack_relay(w_main, relay_src, W, rank, g, plan, slot_src,
+                                               staging, cap, dest_off, status, stream)
+    if rc is not None:
+        return rc if rc == ULTRAEP_OK else _check(rc, "ultraep_pack_relay")
     _pack_need(w_main, W, g, staging, cap, dest_off, status)
     _need(relay_src, g.n_slot * W, 2, "relay_src")
     _need(slot_src, g.R * g.n_slot, 4, "slot_src")
@@ -320,6 +388,10 @@ def ultraep_pack_relay(w_main, relay_src, W, rank, g: Group, plan: Plan, slot_sr
 
 
 def ultraep_combine(y, n_rows, gate, row_of_slot, T, k, H, out, status, stream=None):
+    rc = (_native or _load_native()).combine(y, n_rows, gate, row_of_slot, T, k, H, out, status,
+                                            stream)
+    if rc is not None:
+        return rc if rc == ULTRAEP_OK else _check(rc, "ultraep_combine")
     _need(y, n_rows * H, 2, "y")
     _need(gate, T * k, 4, "gate")
     _need(row_of_slot, T * k, 4, "row_of_slot")
@@ -332,6 +404,10 @@ def ultraep_combine(y, n_rows, gate, row_of_slot, T, k, H, out, status, stream=N
 
 def ultraep_grad_reduce(main_grad, rgrad, W, rank, g: Group, plan: Plan, cap, status,
                         stream=None):
+    rc = (_native or _load_native()).grad_reduce(main_grad, rgrad, W, rank, g, plan, cap, status,
+                                                stream)
+    if rc is not None:
+        return rc if rc == ULTRAEP_OK else _check(rc, "ultraep_grad_reduce")
     _need(main_grad, g.n_main * W, 4, "main_grad")
     _need(rgrad, cap * W, 4, "rgrad")
     _need(status, 1, 4, "status")
@@ -343,6 +419,6 @@ def ultraep_grad_reduce(main_grad, rgrad, W, rank, g: Group, plan: Plan, cap, st
 def build():
     """Compile libultraep.so for gfx950 in-tree."""
     from . import _build
-    global _lib
-    _lib = None
+    global _lib, _native
+    _lib = _native = None
     return _build.build()

@@ -1,4 +1,5 @@
-"""Build libultraep.so in-tree with hipcc for gfx950."""
+"""Build libultraep.so (hipcc, gfx950) and the native half of the Python binding
+(_native.so, the host compiler) in-tree."""
 from __future__ import annotations
 
 import concurrent.futures as cf
@@ -8,6 +9,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libultraep.so")
+NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["abi.hip", "count.hip", "plan.hip", "dispatch.hip", "pack.hip",
            "relay.hip", "combine.hip", "reduce.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -17,6 +19,27 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
 # the fp32 steps round every product and sum on its own: no contraction into
 # fused multiply-adds (the other sources have no fp32 arithmetic to fuse)
 EXTRA = {"combine.hip": ["-ffp-contract=off"], "reduce.hip": ["-ffp-contract=off"]}
+
+
+def build_native() -> str:
+    """csrc/binding.cpp against torch's headers and libraries."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *(f"-isystem{d}" for d in cpp_extension.include_paths()),
+           f"-isystem{sysconfig.get_paths()['include']}", "-isystem/opt/rocm/include",
+           os.path.join(CSRC, "binding.cpp"), f"-L{libs}", "-ltorch_python", "-ltorch_cpu",
+           "-lc10", "-lc10_hip", f"-Wl,-rpath,{libs}", "-o", NATIVE + ".tmp"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"building the binding failed:\n{r.stderr}")
+    os.replace(NATIVE + ".tmp", NATIVE)
+    return NATIVE
 
 
 def build(verbose: bool = False) -> str:
@@ -33,8 +56,10 @@ def build(verbose: bool = False) -> str:
             print(r.stderr)
         return obj
 
-    with cf.ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with cf.ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as ex:
+        native = ex.submit(build_native)
         objs = list(ex.map(compile_one, SOURCES))
+        native.result()
     tmp = LIB + ".tmp"
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -85,3 +85,16 @@ def test_combine_and_reduce_buffers():
     with pytest.raises(ValueError, match="rgrad"):
         uep.ultraep_grad_reduce(t(32, torch.float32), t(2 * 8, torch.int16), 8, 0, G, None, 2,
                                 t(1))
+
+
+def test_native_half_declines_host_tensors():
+    """What the native half does not take it leaves to the code above: host
+    tensors, missing ones, too few arguments and other types give None."""
+    n = uep._load_native()
+    assert n.count(t(40), 10, 2, 16, 2, t(32), t(1), 0) is None
+    assert n.count(None, 0, 2, 16, 2, None, None, 0) is None
+    assert n.count(t(40), 10.0, 2, 16, 2, t(32), t(1), 0) is None
+    assert n.count(t(40), 1 << 70, 2, 16, 2, t(32), t(1), 0) is None
+    assert n.count(t(40)) is None
+    assert n.plan(t(64), G, object(), None, 0) is None
+    assert n.plan(t(64), (4, 16, 2, 8), None, None, 0) is None
