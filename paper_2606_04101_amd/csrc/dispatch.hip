@@ -8,10 +8,16 @@
 //                prefix block_off, and per CSR entry the cumulative quota C
 //                and the first row minus the entry's starting ordinal.
 //   k_dl_rows  : workgroup c sums the histograms of chunks < c (its base
-//                ordinal per expert), then each wave ranks its 128 slots
+//                ordinal per expert; all threads share the chunks, and the
+//                loads past the first four per thread are skipped when
+//                there are no such chunks: code that runs once costs its
+//                fetch), then each wave ranks its 128 slots
 //                stably with ballot matches (wave-private running counts in
 //                LDS, scanned across waves), finds the first instance whose
 //                cumulative quota exceeds the ordinal and writes the row.
+//   Both kernels (graph of 20 calls, one rank): 9.3 us for 32768 slots of
+//   E = 256 and 11.7 us for 131072; 9.8 and 13.5 us with one thread per expert
+//   in the sums and all of its loads unrolled.
 // Scatter (bandwidth bound): persistent waves walk the tokens; a wave holds
 //   one token's row in registers (16-byte non-temporal loads) while the next
 //   token's row is being loaded, and stores each 1 KiB chunk to all k
@@ -34,7 +40,8 @@ static_assert(kSlotsPerWave % kWave == 0, "chunk must split into wave steps");
 // CSR columns (E + R * n_slot <= 1024 + 256) and start pointers (E + 1) per
 // thread when a 1024-thread workgroup stages them
 constexpr int kLutIters = 2;
-constexpr int kSumBatch = 16;  // chunk histograms summed per batch of loads
+constexpr int kSumFirst = 4;   // chunk histograms per thread in the first loads
+constexpr int kSumBatch = 12;  // and in each further batch
 static_assert(kLutIters * kDlThreads >= 1024 + 256 && kLutIters * kDlThreads >= 1024 + 1,
               "the lookup tables fit the staging loops");
 constexpr int kSteps = kSlotsPerWave / kWave;  // 64-slot steps per wave
@@ -63,6 +70,7 @@ struct DlArgs {
   const int32_t *topk;
   int64_t V;
   int32_t rank, R, E, NS, nm, S, ncol, nbits;
+  int32_t parts, div_E;  // threads per expert in the sums over chunks, 2^20 / E rounded up
   int32_t stage_lut;  // copy host_ptr / entry tables into LDS
   const int32_t *hp, *hr, *hs, *q;  // q = reroute row of `rank`
   int32_t *row_of_slot;
@@ -71,23 +79,27 @@ struct DlArgs {
   int32_t *status;
 };
 
+// Sum of the first row's 16 lanes, in every lane.
+__device__ __forceinline__ int row_first_sum(int v) { return readlane(row_sum(v), 0); }
+static_assert(kDlWaves == 16, "the waves' totals fill one row of lanes");
+
 __global__ void __launch_bounds__(kDlThreads) k_dl_hist(DlArgs a) {
   extern __shared__ int32_t lds[];
   const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
   const int E = a.E;
   if (blockIdx.x < a.ws.n_chunks) {
     int32_t *hist = lds;  // [kDlWaves][E]
-    for (int i = tid; i < kDlWaves * E; i += kDlThreads) hist[i] = 0;
-    __syncthreads();
     const int64_t c0 = static_cast<int64_t>(blockIdx.x) * kDispatchChunk;
     int32_t *wh = hist + wave * E;
     bool bad = false;
-    int32_t ev[kSteps];
+    int32_t ev[kSteps];  // on their way while the bins are cleared
 #pragma unroll
     for (int s = 0; s < kSteps; ++s) {
       const int64_t i = c0 + wave * kSlotsPerWave + s * kWave + lane;
       ev[s] = i < a.V ? a.topk[i] : -1;
     }
+    for (int i = tid; i < kDlWaves * E; i += kDlThreads) hist[i] = 0;
+    __syncthreads();
 #pragma unroll
     for (int s = 0; s < kSteps; ++s) {
       const int32_t e = ev[s];
@@ -99,6 +111,7 @@ __global__ void __launch_bounds__(kDlThreads) k_dl_hist(DlArgs a) {
     int32_t *dst = a.ws.hist + blockIdx.x * static_cast<int64_t>(E);
     for (int e = tid; e < E; e += kDlThreads) {
       int s = 0;
+#pragma unroll
       for (int w = 0; w < kDlWaves; ++w) s += hist[w * E + e];
       dst[e] = s;
     }
@@ -111,7 +124,7 @@ __global__ void __launch_bounds__(kDlThreads) k_dl_hist(DlArgs a) {
   const int ncol = a.ncol;
   int32_t *cnt = lds;                  // [R*S]
   int32_t *tmp = lds + kMaxBlocks;     // [kDlWaves]
-  int32_t *l_hp = tmp + kDlWaves + 1;  // [E + 1]
+  int32_t *l_hp = tmp + kDlWaves;      // [E + 1]
   int32_t *l_hr = l_hp + E + 1;        // [ncol]
   int32_t *l_hs = l_hr + ncol;         // [ncol]
   int32_t *l_q = l_hs + ncol;          // [ncol]
@@ -160,17 +173,8 @@ __global__ void __launch_bounds__(kDlThreads) k_dl_hist(DlArgs a) {
   const int incl = wave_scan_incl(v0 + v1);
   if (lane == kWave - 1) tmp[wave] = incl;
   __syncthreads();
-  if (tid == 0) {
-    int run = 0;
-    for (int w = 0; w < kDlWaves; ++w) {
-      int t = tmp[w];
-      tmp[w] = run;
-      run += t;
-    }
-  }
-  __syncthreads();
-  const int ex0 = tmp[wave] + incl - v0 - v1;
-  __syncthreads();
+  const int wtot = lane < wave ? tmp[lane & (kDlWaves - 1)] : 0;  // totals of the waves before
+  const int ex0 = row_first_sum(wtot) + incl - v0 - v1;
   // reuse cnt as offsets
   if (b0 < nblk) cnt[b0] = ex0;
   if (b1 < nblk) cnt[b1] = ex0 + v0;
@@ -196,23 +200,31 @@ __global__ void __launch_bounds__(kDlThreads) k_dl_rows(DlArgs a) {
   const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
   const int E = a.E, ncol = a.ncol;
   const int c = blockIdx.x;
-  int32_t *whist = lds;  // [kDlWaves][E]
-  int32_t *base = lds + kDlWaves * E;
+  int32_t *whist = lds;                  // [kDlWaves][E]
+  int32_t *psum = lds + kDlWaves * E;    // [kDlThreads] partial sums over chunks
   // Every input is requested at once (indices clamped into range, no branch
   // between the loads), so the workgroup waits for memory once: its slots'
   // expert ids, the histograms of the chunks before it (of every chunk in
-  // workgroup 0, which checks them against the expected totals) and the
+  // workgroup 0, which checks them against the expected totals; thread
+  // (part, e) takes chunks part, part + parts, ... of expert e) and the
   // instance lookup tables.
   const int64_t s0 = static_cast<int64_t>(c) * kDispatchChunk + wave * kSlotsPerWave;
   int32_t ev[kSteps];
 #pragma unroll
   for (int s = 0; s < kSteps; ++s) ev[s] = a.topk[min(s0 + s * kWave + lane, a.V - 1)];
-  const int e_t = min(tid, E - 1);  // this thread's expert for the sums (tid < E)
+  const int parts = a.parts;
+  const int part = (tid * a.div_E) >> 20, e_t = tid - part * E;  // tid / E, tid % E
   const int nsum = c == 0 ? static_cast<int>(a.ws.n_chunks) : c;
   const int32_t *h = a.ws.hist + e_t;
-  int hv[kSumBatch];
+  const bool many = nsum > kSumFirst * parts;  // else the other loads are skipped
+  int hv[kSumFirst], hw[kSumBatch];
 #pragma unroll
-  for (int u = 0; u < kSumBatch; ++u) hv[u] = h[min(u, nsum - 1) * static_cast<int64_t>(E)];
+  for (int u = 0; u < kSumFirst; ++u) hv[u] = h[min(part + u * parts, nsum - 1) * E];
+  if (many) {
+#pragma unroll
+    for (int u = 0; u < kSumBatch; ++u)
+      hw[u] = h[min(part + (kSumFirst + u) * parts, nsum - 1) * static_cast<int64_t>(E)];
+  }
   const int exp_tot = c == 0 ? a.ws.exp_tot[e_t] : 0;
   int vhp[kLutIters], vcum[kLutIters], vbase[kLutIters];
   if (a.stage_lut) {
@@ -226,13 +238,20 @@ __global__ void __launch_bounds__(kDlThreads) k_dl_rows(DlArgs a) {
       }
     }
   }
+  for (int i = tid; i < kDlWaves * E; i += kDlThreads) whist[i] = 0;
+  __syncthreads();
+  int32_t *wh = whist + wave * E;
+  // pass 1: per-wave counts
 #pragma unroll
-  for (int s = 0; s < kSteps; ++s)
+  for (int s = 0; s < kSteps; ++s) {
     if (s0 + s * kWave + lane >= a.V) ev[s] = -1;
+    const int32_t e = ev[s];
+    if (e >= 0 && e < E) atomicAdd(wh + e, 1);
+  }
   // instance lookup tables, staged in LDS when they fit
   const int32_t *l_hp = a.hp, *l_cum = a.ws.ent_cum, *l_base = a.ws.ent_base;
   if (a.stage_lut) {
-    int32_t *p = base + E;
+    int32_t *p = psum + kDlThreads;
 #pragma unroll
     for (int u = 0; u < kLutIters; ++u) {
       const int ii = u * kDlThreads + tid;
@@ -246,46 +265,41 @@ __global__ void __launch_bounds__(kDlThreads) k_dl_rows(DlArgs a) {
     l_cum = p + E + 1;
     l_base = p + E + 1 + ncol;
   }
-  // base ordinals: sums over the earlier chunks' histograms (further batches
-  // of kSumBatch loads when there are more chunks than one batch)
-  if (tid < E) {
-    int s = 0, tot = 0;
+  // sums over the chunks (further batches of loads when there are more than
+  // kSumBatch chunks per thread)
+  {
+    int s = 0;
 #pragma unroll
-    for (int u = 0; u < kSumBatch; ++u) {
-      const int v = u < nsum ? hv[u] : 0;
-      s += u < c ? v : 0;
-      tot += v;
-    }
-    for (int c0 = kSumBatch; c0 < nsum; c0 += kSumBatch) {
-      int w[kSumBatch];
+    for (int u = 0; u < kSumFirst; ++u) s += part + u * parts < nsum ? hv[u] : 0;
+    if (many) {
+      int c0 = part + kSumFirst * parts;
+      for (;;) {
 #pragma unroll
-      for (int u = 0; u < kSumBatch; ++u) w[u] = h[min(c0 + u, nsum - 1) * static_cast<int64_t>(E)];
+        for (int u = 0; u < kSumBatch; ++u) s += c0 + u * parts < nsum ? hw[u] : 0;
+        c0 += kSumBatch * parts;
+        if (c0 - part >= nsum) break;
 #pragma unroll
-      for (int u = 0; u < kSumBatch; ++u) {
-        const int v = c0 + u < nsum ? w[u] : 0;
-        s += c0 + u < c ? v : 0;
-        tot += v;
+        for (int u = 0; u < kSumBatch; ++u)
+          hw[u] = h[min(c0 + u * parts, nsum - 1) * static_cast<int64_t>(E)];
       }
     }
-    base[tid] = s;
-    if (c == 0 && tot != exp_tot) report(a.status, ULTRAEP_EDATA);
+    psum[tid] = s;
   }
-  for (int i = tid; i < kDlWaves * E; i += kDlThreads) whist[i] = 0;
   __syncthreads();
-  int32_t *wh = whist + wave * E;
-  // pass 1: per-wave counts
+  // base ordinals, then every wave's start in the chunk
+  if (tid < E) {
+    int run = 0, w[kDlWaves];
+    for (int p = 0; p < parts; ++p) run += psum[p * E + tid];
+    if (c == 0) {
+      if (run != exp_tot) report(a.status, ULTRAEP_EDATA);
+      run = 0;
+    }
 #pragma unroll
-  for (int s = 0; s < kSteps; ++s) {
-    const int32_t e = ev[s];
-    if (e >= 0 && e < E) atomicAdd(wh + e, 1);
-  }
-  __syncthreads();
-  for (int e = tid; e < E; e += kDlThreads) {
-    int run = base[e];
-    for (int w = 0; w < kDlWaves; ++w) {
-      int t = whist[w * E + e];
-      whist[w * E + e] = run;
-      run += t;
+    for (int i = 0; i < kDlWaves; ++i) w[i] = whist[i * E + tid];
+#pragma unroll
+    for (int i = 0; i < kDlWaves; ++i) {
+      whist[i * E + tid] = run;
+      run += w[i];
     }
   }
   __syncthreads();
@@ -338,6 +352,10 @@ hipError_t launch_dispatch_layout(const int32_t *topk, int64_t V, int32_t rank,
   a.S = a.nm + g.n_slot;
   a.ncol = g.E + g.R * g.n_slot;
   a.nbits = bits_for(g.E);
+  // tid * div_E >> 20 is tid / E for tid < 1024: the excess of the product
+  // over tid * 2^20 / E is below tid, so below 2^20 / E
+  a.parts = kDlThreads / g.E;
+  a.div_E = ((1 << 20) + g.E - 1) / g.E;
   a.hp = plan.host_ptr;
   a.hr = plan.host_rank;
   a.hs = plan.host_pslot;
@@ -349,12 +367,12 @@ hipError_t launch_dispatch_layout(const int32_t *topk, int64_t V, int32_t rank,
   a.stage_lut = 0;
   const size_t lds_hist = sizeof(int32_t) * kDlWaves * g.E;
   const size_t lds_lay =
-      sizeof(int32_t) * (kMaxBlocks + kDlWaves + 1 + g.E + 1 + 3 * static_cast<size_t>(a.ncol));
+      sizeof(int32_t) * (kMaxBlocks + kDlWaves + g.E + 1 + 3 * static_cast<size_t>(a.ncol));
   hipLaunchKernelGGL(k_dl_hist, dim3(ws.n_chunks + 1), dim3(kDlThreads),
                      lds_hist > lds_lay ? lds_hist : lds_lay, stream, a);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess || ws.n_chunks == 0) return err;
-  size_t lds_rows = sizeof(int32_t) * (kDlWaves + 1) * g.E;
+  size_t lds_rows = sizeof(int32_t) * (kDlWaves * static_cast<size_t>(g.E) + kDlThreads);
   const size_t lut = sizeof(int32_t) * (g.E + 1 + 2 * static_cast<size_t>(a.ncol));
   if (lds_rows + lut <= 64 * 1024) {
     lds_rows += lut;

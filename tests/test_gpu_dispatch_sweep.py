@@ -148,3 +148,24 @@ def test_scatter_units(T, k, H):
     ref = np.zeros((V, H), np.uint16)
     ref[ros[routed]] = x[np.arange(V)[routed] // k]
     assert np.array_equal(gp.host_u16(send), ref)
+
+
+# the sums over chunk histograms: threads per expert from 1 to many, chunk
+# counts around the first batch of loads and over several batches
+@pytest.mark.parametrize("R,E", [(1, 1), (3, 6), (8, 128), (4, 300), (8, 1000), (16, 1024)])
+@pytest.mark.parametrize("T", [1, 2049, 4 * 2048, 4 * 2048 + 1, 18 * 2048 + 77, 70 * 2048])
+def test_layout_chunk_sums(R, E, T):
+    rng = np.random.default_rng(T + E)
+    tk = np.minimum(rng.geometric(min(1.0, 8 / E), (R, T, 1)) - 1, E - 1).astype(np.int32)
+    tk[rng.random(tk.shape) < 0.1] = -1
+    g, og = gp.groups(R, E, 1, max(1, T // 64))
+    load, _ = oracle.count(tk, E, R)
+    op = oracle.plan(load, og)
+    plan = gp.gpu_plan(load, g)
+    x = (np.arange(T * 8) & 0xFFFF).astype(np.uint16).reshape(T, 8)
+    rank = R - 1
+    send, ros, off, st = gp.gpu_dispatch(x, tk[rank], rank, g, plan)
+    assert st == 0
+    osend, oros, ooff, ost = oracle.dispatch(x, tk[rank], rank, og, op)
+    assert np.array_equal(ros, oros) and np.array_equal(off, ooff)
+    assert np.array_equal(send, osend)
