@@ -19,20 +19,37 @@
 //     smallest volume (ties to the smaller rank), counted at once;
 //   - after the expert, the source's volume drops by f minus the relays.
 //
-// One workgroup.  All threads validate the plan's host lists, seed the
-// slot senders and volumes in LDS and sort the hot experts (a compacted
-// list, ranked by counting).  The experts then depend on each other only
-// through the volumes, so one wave walks them in order: a replica per lane
-// (f <= R - 1 <= 63), relays chosen by each lane counting the lanes with a
-// smaller (volume, rank) key, leaves attached one after another with a wave
-// minimum over the relays' keys.
+// One workgroup; what bounds it is the chain of dependent latencies, not
+// work.  Every input is requested at once and staged in LDS, so memory is
+// waited for once.  The host lists are validated a column per thread: a home
+// column must be its expert's first one, a replica column must lie behind it in
+// the list of the expert that its slot holds, at ascending ranks (walking each
+// list in one thread waited for memory once per replica).  The hot experts are
+// compacted and ranked by counting.  They depend on each other only through
+// the volumes, so one wave walks them in order, a host per lane (f + 1 <= R <=
+// 64).  The n relays are n wave minima over (volume, rank).  The leaves need no
+// order of their own: dealing them one by one to the smallest (volume, rank)
+// hands out the merged keys (V_i + q, rank) of the relays in ascending order, so
+// with the relays sorted and C_i the number of keys below volume V_i, leaf m
+// falls among relays 0..i for the last i with C_i <= m, at place (m - C_i)
+// mod (i + 1) by rank.
+// Each expert's columns are read while the expert before it is dealt.
+// Graph of 20 calls: 3.3 us without a hot expert at R = 64, E = 128 (3.9 with a
+// list per thread and leaves one by one), 5.4 with two hot experts at R = 32,
+// E = 256 (7.5), 12.9 with five of fan-outs up to 63 (54.3), 19.7 with twelve
+// at E = 256 (47.8), 32.7 with thirty at R = 16, E = 1024 (48.9).
 #include "common.hpp"
 #include "kernels.hpp"
 
 namespace uep {
 
 constexpr int kRlThreads = 1024;
-constexpr int kRlMaxSlots = 256;   // R * n_slot
+constexpr int kRlMaxE = 1024;
+constexpr int kRlMaxSlots = 256;                   // R * n_slot
+constexpr int kRlMaxCol = kRlMaxE + kRlMaxSlots;   // host-list columns
+constexpr int kRlColIters = 2;                     // columns per thread
+static_assert(kRlThreads >= kRlMaxE && kRlColIters * kRlThreads >= kRlMaxCol,
+              "an expert and its columns fit the threads");
 
 struct RlArgs {
   int32_t R, E, NS, nm, ncol, threshold;
@@ -43,123 +60,190 @@ struct RlArgs {
   int32_t *status;
 };
 
-__device__ __forceinline__ int nearest_sqrt(int f) {
-  int n = 0;
-  while ((n + 1) * (n + 1) <= f) ++n;
-  return f > n * n + n ? n + 1 : n;
-}
-
+// The minimum of the 64 lanes, uniform: rows of 16 by DPP mirrors, then across
+// the rows by DPP broadcasts into lane 63.  Every lane must be active.
 __device__ __forceinline__ int wave_min(int v) {
   v = min(v, __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xF, 0xF, false));   // quad_perm 1,0,3,2
   v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xF, 0xF, false));   // quad_perm 2,3,0,1
   v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x141, 0xF, 0xF, false));  // row_half_mirror
   v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x140, 0xF, 0xF, false));  // row_mirror
-  int a = readlane(v, 0), b = readlane(v, 16), c = readlane(v, 32), d = readlane(v, 48);
-  return __builtin_amdgcn_readfirstlane(min(min(a, b), min(c, d)));
+  v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x142, 0xA, 0xF, false));  // row_bcast:15
+  v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xC, 0xF, false));  // row_bcast:31
+  return readlane(v, 63);
 }
 
 __global__ void __launch_bounds__(kRlThreads) k_relay(RlArgs a) {
+  __shared__ int32_t s_hp[kRlMaxE + 1];
+  __shared__ int32_t s_hr[kRlMaxCol];
+  __shared__ int32_t s_hs[kRlMaxCol];
+  __shared__ int32_t s_x[kRlMaxSlots];
   __shared__ int32_t s_src[kRlMaxSlots];
   __shared__ int32_t s_vol[kWave];
   __shared__ int32_t s_hot[kRlMaxSlots];   // hot experts, unsorted
   __shared__ int32_t s_ord[kRlMaxSlots];   // sorted
   __shared__ int32_t s_wcnt[kRlThreads / kWave];
-  __shared__ int32_t s_bad, s_nhot;
   const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
-  const int R = a.R, E = a.E, NS = a.NS, nm = a.nm, RS = R * NS;
-  if (tid < kWave) s_vol[tid] = 0;
-  if (tid == 0) {
-    s_bad = a.plan_stats[6] != 0;
-    s_nhot = 0;
+  const int R = a.R, E = a.E, NS = a.NS, nm = a.nm, RS = R * NS, ncol = a.ncol;
+  // inputs, indices clamped into range
+  int vr[kRlColIters], vs[kRlColIters];
+#pragma unroll
+  for (int u = 0; u < kRlColIters; ++u) {
+    if (u * kRlThreads < ncol) {
+      const int j = min(u * kRlThreads + tid, ncol - 1);
+      vr[u] = a.hr[j];
+      vs[u] = a.hs[j];
+    }
   }
+  const int vp = a.hp[min(tid, E)], total = a.hp[E];
+  const int vx = tid < RS ? a.X[tid] : -1;
+  bool bad = a.plan_stats[6] != 0;
+  if (tid < kWave) s_vol[tid] = 0;
+#pragma unroll
+  for (int u = 0; u < kRlColIters; ++u) {
+    const int j = u * kRlThreads + tid;
+    if (j < ncol) {
+      s_hr[j] = vr[u];
+      s_hs[j] = vs[u];
+    }
+  }
+  if (tid < E) s_hp[tid] = vp;
+  if (tid == 0) s_hp[E] = total;
+  if (tid < RS) s_x[tid] = vx;
   __syncthreads();
-  // host lists: home first, then replicas by ascending rank on the slot
-  // that holds the expert
-  const int total = a.hp[E];
-  if (a.hp[0] != 0 || total < E || total > a.ncol) s_bad = 1;
+  // The pointers start at 0, ascend and end within the columns, a list has at
+  // most R entries; then every column below `total` is in one expert's list
+  // and the checks of the columns are those of the lists.
+  bad |= total > ncol;
   int f = -1;
   if (tid < E) {
-    const int e = tid, h = e / nm;
-    const int j0 = a.hp[e], j1 = a.hp[e + 1];
-    bool ok = j0 >= 0 && j1 > j0 && j1 <= a.ncol && j1 - j0 <= R;
-    if (ok) ok = a.hr[j0] == h && a.hs[j0] == e - h * nm;
-    for (int j = j0 + 1; ok && j < j1; ++j) {
-      const int t = a.hr[j], s = a.hs[j] - nm;
-      ok = t >= 0 && t < R && t != h && s >= 0 && s < NS && a.X[t * NS + s] == e &&
-           (j == j0 + 1 || t > a.hr[j - 1]);
+    f = static_cast<int>(static_cast<uint32_t>(s_hp[tid + 1]) - static_cast<uint32_t>(vp) - 1u);
+    bad |= f < 0 || f >= R || (tid == 0 && vp != 0);
+  }
+#pragma unroll
+  for (int u = 0; u < kRlColIters; ++u) {
+    const int j = u * kRlThreads + tid;
+    if (j < min(total, ncol)) {
+      const int t = vr[u], s = vs[u];
+      bool ok = t >= 0 && t < R && s >= 0 && s < nm + NS;
+      if (ok && s < nm) {
+        ok = s_hp[t * nm + s] == j;  // the home column: the first of its expert
+      } else if (ok) {
+        const int e = s_x[t * NS + s - nm];
+        ok = e >= 0 && e < E && e / nm != t;
+        if (ok) {
+          const int j0 = s_hp[e];
+          ok = j > j0 && j < s_hp[e + 1] && (j == j0 + 1 || t > s_hr[j - 1]);
+        }
+      }
+      bad |= !ok;
     }
-    if (!ok) s_bad = 1;
-    else f = j1 - j0 - 1;
   }
   // senders start at the home ranks; volumes count one blob per replica
   if (tid < RS) {
-    const int e = a.X[tid];
-    const bool ok = e >= -1 && e < E;
-    if (!ok) s_bad = 1;
-    const int h = ok && e >= 0 ? e / nm : -1;
+    const bool ok = vx >= -1 && vx < E;
+    bad |= !ok;
+    const int h = ok && vx >= 0 ? vx / nm : -1;
     s_src[tid] = h;
     if (h >= 0) atomicAdd(&s_vol[h], 1);
   }
-  // compact the hot experts
   const bool hot = f > a.threshold;
   const uint64_t hb = ballot(hot);
   if (lane == 0) s_wcnt[wave] = __popcll(hb);
-  __syncthreads();
-  if (s_bad) {
+  if (__syncthreads_or(bad)) {
     if (tid == 0) report(a.status, ULTRAEP_EDATA);
     return;
   }
-  int pos = popc_below(hb);
-  for (int w = 0; w < wave; ++w) pos += s_wcnt[w];
-  if (hot) s_hot[pos] = tid;
-  if (tid == kRlThreads - 1) {
-    int n = 0;
-    for (int w = 0; w < kRlThreads / kWave; ++w) n += s_wcnt[w];
-    s_nhot = n;
+  // compact the hot experts
+  int pos = popc_below(hb), nhot = 0;
+  for (int w = 0; w < kRlThreads / kWave; ++w) {
+    const int n = s_wcnt[w];
+    pos += w < wave ? n : 0;
+    nhot += n;
   }
-  __syncthreads();
-  const int nhot = s_nhot;
-  // order: replica count descending, then id ascending (rank by counting)
-  if (tid < nhot) {
-    const int e = s_hot[tid], fe = a.hp[e + 1] - a.hp[e];
-    int r = 0;
-    for (int i = 0; i < nhot; ++i) {
-      const int o = s_hot[i], fo = a.hp[o + 1] - a.hp[o];
-      r += fo > fe || (fo == fe && o < e);
-    }
-    s_ord[r] = e;
-  }
-  int vmax0 = 0;
+  int vmax0 = 0, n_relays = 0;
   if (wave == 0) vmax0 = wave_max(lane < R ? s_vol[lane] : 0);
-  __syncthreads();
-  int n_relays = 0;
-  if (wave == 0) {
-    for (int hi = 0; hi < nhot; ++hi) {
-      const int e = s_ord[hi];
-      const int j0 = a.hp[e], fe = a.hp[e + 1] - j0 - 1;
-      const int n = nearest_sqrt(fe);
-      const bool act = lane < fe;
-      const int t = act ? a.hr[j0 + 1 + lane] : 0;
-      const int s = act ? a.hs[j0 + 1 + lane] - nm : 0;
-      int v = act ? s_vol[t] : 0;
-      // relays: the n lanes of smallest (volume, rank)
-      const int key = act ? (v << 6) | t : INT32_MAX;
-      int below = 0;
-      for (int l = 0; l < fe; ++l) below += readlane(key, l) < key;
-      const bool relay = act && below < n;
-      // leaves, ascending rank, each to the relay of smallest (volume, rank)
-      uint64_t leaves = ballot(act && !relay);
-      while (leaves) {
-        const int l = __builtin_ctzll(leaves);
-        leaves &= leaves - 1;
-        const int m = wave_min(relay ? (v << 6) | t : INT32_MAX);
-        const int win = m & 63;
-        if (relay && t == win) v += 1;
-        if (lane == l) s_src[t * NS + s] = win;
+  if (nhot > 0) {  // uniform
+    if (hot) s_hot[pos] = tid;
+    __syncthreads();
+    // order: replica count descending, then id ascending (rank by counting)
+    if (tid < nhot) {
+      const int e = s_hot[tid], fe = s_hp[e + 1] - s_hp[e];
+      int r = 0;
+      for (int i = 0; i < nhot; ++i) {
+        const int o = s_hot[i], fo = s_hp[o + 1] - s_hp[o];
+        r += fo > fe || (fo == fe && o < e);
       }
-      if (relay) s_vol[t] = v;
-      if (lane == 0) s_vol[e / nm] -= fe - n;
-      n_relays += n;
+      s_ord[r] = e;
+    }
+    __syncthreads();
+    if (wave == 0) {
+      const int recip = 65536 / (lane + 1) + 1;  // x / (lane + 1) for x < 64, lane < 8
+      // an expert's home, its replica count and the replicas' ranks and slots,
+      // read while the expert before it is dealt
+      int n_home, n_fe, n_t, n_s;
+      const auto fetch = [&](int hi) {
+        const int e = s_ord[hi], j0 = s_hp[e];
+        n_fe = s_hp[e + 1] - j0 - 1;
+        n_home = s_hr[j0];
+        const int j = j0 + 1 + min(lane, n_fe - 1);
+        n_t = s_hr[j];
+        n_s = s_hs[j] - nm;
+      };
+      fetch(0);
+      for (int hi = 0; hi < nhot; ++hi) {
+        const int fe = __builtin_amdgcn_readfirstlane(n_fe);
+        const int home = n_home, t = n_t, s = n_s;
+        // the integer nearest sqrt(fe): the i >= 0 with i * i + i < fe
+        const int n = __popcll(ballot(lane * lane + lane < fe));
+        const bool act = lane < fe;
+        // relays: the n smallest (volume, rank); lane i keeps C_i and the
+        // set of the ranks of relays 0..i
+        int key = act ? (s_vol[t] << 6) | t : INT32_MAX;
+        fetch(min(hi + 1, nhot - 1));
+        uint64_t set = 0;
+        int C = 0, vprev = 0, l_c = 0, l_lo = 0, l_hi = 0;
+        bool leaf = act;
+        for (int i = 0; i < n; ++i) {
+          const int m = wave_min(key);
+          if (key == m) {
+            key = INT32_MAX;
+            leaf = false;
+          }
+          C += ((m >> 6) - vprev) * i;
+          vprev = m >> 6;
+          set |= uint64_t(1) << (m & 63);
+          if (lane == i) {
+            l_c = C;
+            l_lo = static_cast<int>(set);
+            l_hi = static_cast<int>(set >> 32);
+          }
+        }
+        // leaves, ascending rank
+        const int m = popc_below(ballot(leaf));
+        int off = 0, cnt = 1, rc = 0, lo = 0, hi32 = 0;
+        for (int i = 0; i < n; ++i) {
+          const int Ci = readlane(l_c, i);
+          if (m >= Ci) {
+            off = m - Ci;
+            cnt = i + 1;
+            rc = readlane(recip, i);
+            lo = readlane(l_lo, i);
+            hi32 = readlane(l_hi, i);
+          }
+        }
+        if (leaf) {
+          const int place = off - ((off * rc) >> 16) * cnt;
+          uint64_t rest = (static_cast<uint64_t>(static_cast<uint32_t>(hi32)) << 32) |
+                          static_cast<uint32_t>(lo);
+          for (int u = 0; u < place; ++u) rest &= rest - 1;
+          const int win = __builtin_ctzll(rest);
+          s_src[t * NS + s] = win;
+          atomicAdd(&s_vol[win], 1);
+        }
+        if (lane == 0) s_vol[home] -= fe - n;
+        n_relays += n;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the volumes, to the next expert
+      }
     }
   }
   __syncthreads();

@@ -111,6 +111,65 @@ def test_relay_dense_slot_maps(seed, R, E, NS, n_hot, threshold):
         assert o.stats[0] > 0  # the case does build relay trees
 
 
+@pytest.mark.parametrize("seed,R,E,NS,n_hot", [(6, 64, 1024, 4, 4), (7, 64, 960, 4, 9),
+                                               (8, 64, 1024, 4, 40), (9, 2, 2, 1, 1), (10, 40, 40, 6, 6)])
+@pytest.mark.parametrize("threshold", [0, 1, 12])
+def test_relay_edges_of_the_staging(seed, R, E, NS, n_hot, threshold):
+    """Host lists that need one pass of 1024 threads, two, and all 1280 columns;
+    fan-outs up to 63 (eight relays) on volumes that differ from the start."""
+    g, og = gp.groups(R, E, NS, 1)
+    p = csr_from_slots(R, E, NS, dense_slot_map(seed, R, E, NS, n_hot))
+    check(g, og, plan_on_device(g, p), p, threshold)
+
+
+@pytest.mark.parametrize("what", ["ptr_start", "ptr_descends", "ptr_long", "ptr_past", "ptr_wraps",
+                                  "home_rank", "home_slot", "home_twice", "lists_swapped", "rank_twice",
+                                  "slot_range", "rank_range", "on_home"])
+def test_relay_refuses_broken_host_lists(what):
+    """One fault each in otherwise sound lists: EDATA, outputs untouched."""
+    R, E, NS = 12, 24, 3
+    g, _ = gp.groups(R, E, NS, 1)
+    p = csr_from_slots(R, E, NS, dense_slot_map(3, R, E, NS, 5))
+    hp, hr, hs, X = (np.array(v, np.int32) for v in (p.host_ptr, p.host_rank, p.host_pslot, p.slot_expert))
+    f = np.diff(hp) - 1
+    a, b = [int(e) for e in np.argsort(-f, kind="stable")[:2]]
+    assert f[b] >= 2
+    ja, jb = int(hp[a]), int(hp[b])
+    if what == "ptr_start":
+        hp[0] = 1
+    elif what == "ptr_descends":
+        hp[a] = hp[a + 1] + 1
+    elif what == "ptr_long":
+        hp[a] -= R
+    elif what == "ptr_past":
+        hp[E] = g.E + R * NS + 1
+    elif what == "ptr_wraps":
+        hp[a] = -2 ** 31
+    elif what == "home_rank":
+        hr[ja] = (hr[ja] + 1) % R
+    elif what == "home_slot":
+        hs[ja] ^= 1
+    elif what == "home_twice":
+        hr[ja + 1], hs[ja + 1] = hr[ja], hs[ja]
+    elif what == "lists_swapped":
+        for v in (hr, hs):
+            v[ja + 1], v[jb + 1] = v[jb + 1], v[ja + 1]
+    elif what == "rank_twice":
+        hr[ja + 2], hs[ja + 2] = hr[ja + 1], hs[ja + 1]
+    elif what == "slot_range":
+        hs[ja + 1] = g.n_main + NS
+    elif what == "rank_range":
+        hr[ja + 1] = -1
+    else:  # a replica on its own home rank
+        home = a // g.n_main
+        X[home, 0] = a
+        hr[ja + 1], hs[ja + 1] = home, g.n_main
+    p.host_ptr, p.host_rank, p.host_pslot, p.slot_expert = hp, hr, hs, X
+    src, vol, stats, st = gpu_relay(g, plan_on_device(g, p), 1)
+    assert st == uep.ULTRAEP_EDATA
+    assert (src == -9).all() and (vol == -9).all() and (stats == -9).all()
+
+
 def test_relay_hand_cases():
     """The hand-derived oracle pins, through the library."""
     R, E, NS = 8, 8, 2
