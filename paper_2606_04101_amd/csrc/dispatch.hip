@@ -5,19 +5,21 @@
 //   k_dl_hist  : workgroup c < n_chunks counts the expert ids of slots
 //                [c*2048, (c+1)*2048); the last workgroup turns row `rank` of
 //                the reroute split into block sizes (t, p), their exclusive
-//                prefix block_off, and per CSR entry the cumulative quota C
-//                and the first row minus the entry's starting ordinal.
+//                prefix block_off, and per CSR entry the running share over
+//                all columns and the first row minus the entry's start in it.
 //   k_dl_rows  : workgroup c sums the histograms of chunks < c (its base
 //                ordinal per expert; all threads share the chunks, and the
 //                loads past the first four per thread are skipped when
 //                there are no such chunks: code that runs once costs its
 //                fetch), then each wave ranks its 128 slots
 //                stably with ballot matches (wave-private running counts in
-//                LDS, scanned across waves), finds the first instance whose
-//                cumulative quota exceeds the ordinal and writes the row.
-//   Both kernels (graph of 20 calls, one rank): 9.3 us for 32768 slots of
-//   E = 256 and 11.7 us for 131072; 9.8 and 13.5 us with one thread per expert
-//   in the sums and all of its loads unrolled.
+//                LDS, scanned across waves), bisects for the first
+//                instance whose running share exceeds the ordinal and writes
+//                the row.
+//   Both kernels (graph of 20 calls, one rank of R = 64): 9.3 us for 32768 slots
+//   of E = 256 and 10.4 us for 131072; 10.1 and 11.2 us with the shares of an
+//   expert summed by one thread and its instances searched one by one, and 13.0
+//   for the latter with the sums over chunks in one thread per expert too.
 // Scatter (bandwidth bound): persistent waves walk the tokens; a wave holds
 //   one token's row in registers (16-byte non-temporal loads) while the next
 //   token's row is being loaded, and stores each 1 KiB chunk to all k
@@ -83,6 +85,182 @@ struct DlArgs {
 __device__ __forceinline__ int row_first_sum(int v) { return readlane(row_sum(v), 0); }
 static_assert(kDlWaves == 16, "the waves' totals fill one row of lanes");
 
+// This rank's layout tables in LDS.
+struct DlTables {
+  int32_t *cnt;  // [kMaxBlocks] rows per (rank, slot) block, then its first row
+  int32_t *tmp;  // [2 * kDlWaves]
+  int32_t *hp;   // [E + 1]
+  int32_t *hr;   // [ncol] host rank, then the entry's first row minus P
+  int32_t *hs;   // [ncol] its slot
+  int32_t *q;    // [ncol] this rank's share, then P + share
+};
+
+__host__ __device__ __forceinline__ int lut_ints(int E, int ncol) {
+  return kMaxBlocks + 2 * kDlWaves + E + 1 + 3 * ncol;
+}
+
+__device__ __forceinline__ DlTables carve_tables(int32_t *p, int E, int ncol) {
+  DlTables t;
+  t.cnt = p;
+  t.tmp = t.cnt + kMaxBlocks;
+  t.hp = t.tmp + 2 * kDlWaves;
+  t.hr = t.hp + E + 1;
+  t.hs = t.hr + ncol;
+  t.q = t.hs + ncol;
+  return t;
+}
+
+// The inputs of the tables: requested at once (indices clamped into range, no
+// branch between the loads), then staged in LDS.
+struct DlInputs {
+  int hp[kLutIters], hr[kLutIters], hs[kLutIters], q[kLutIters];
+  __device__ __forceinline__ void load(const DlArgs &a) {
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < kLutIters; ++u) {
+      if (u * kDlThreads <= a.E) hp[u] = a.hp[min(u * kDlThreads + tid, a.E)];
+      if (u * kDlThreads < a.ncol) {
+        const int j = min(u * kDlThreads + tid, a.ncol - 1);
+        hr[u] = a.hr[j];
+        hs[u] = a.hs[j];
+        q[u] = a.q[j];
+      }
+    }
+  }
+  __device__ __forceinline__ void stage(const DlArgs &a, const DlTables &t) const {
+#pragma unroll
+    for (int u = 0; u < kLutIters; ++u) {
+      const int i = u * kDlThreads + threadIdx.x;
+      if (i <= a.E) t.hp[i] = hp[u];
+      if (i < a.ncol) {
+        t.hr[i] = hr[u];
+        t.hs[i] = hs[u];
+        t.q[i] = q[u];
+      }
+    }
+  }
+};
+
+// Block sizes and offsets, and per CSR column the running share over ALL
+// columns: with P the shares of the columns before it, a slot of expert e with
+// ordinal o belongs to the first column of e whose P + share exceeds
+// P(first column of e) + o, and its row is that sum plus the block's first row
+// minus the column's P.  One block scan gives every P (a loop over an
+// expert's columns in one thread took a chain of LDS reads per replica).  The
+// inputs are staged and cnt is cleared, before a barrier; the tables are
+// complete at the return.  False: not a plan of this group.
+__device__ __forceinline__ bool build_tables(const DlArgs &a, const DlTables &t, bool writes) {
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+  const int E = a.E, ncol = a.ncol, nblk = a.R * a.S;
+  // the CSR must start at 0, never decrease and end within the columns,
+  // so every entry index below is inside the tables
+  const int total = t.hp[E];
+  bool bad = t.hp[0] != 0 || total < E || total > ncol;
+  for (int e = tid; e < E; e += kDlThreads) bad |= t.hp[e] > t.hp[e + 1];
+  if (__syncthreads_or(bad)) return false;
+  static_assert(2 * kDlThreads >= kMaxBlocks && 2 * kDlThreads >= 1024 + 256,
+                "two blocks and two columns per thread");
+  const int j0 = 2 * tid, j1 = 2 * tid + 1;
+  int blk[2], q[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int j = 2 * tid + u;
+    blk[u] = -1;
+    q[u] = 0;
+    if (j < total) {
+      const int r = t.hr[j], p = t.hs[j];
+      q[u] = t.q[j];
+      if (r >= 0 && r < a.R && p >= 0 && p < a.S) {
+        blk[u] = r * a.S + p;
+        t.cnt[blk[u]] = q[u];
+      } else if (writes) {
+        report(a.status, ULTRAEP_EDATA);
+      }
+    }
+  }
+  __syncthreads();
+  // exclusive scans, two elements per thread
+  const int v0 = j0 < nblk ? t.cnt[j0] : 0, v1 = j1 < nblk ? t.cnt[j1] : 0;
+  const int incl = wave_scan_incl(v0 + v1), inclq = wave_scan_incl(q[0] + q[1]);
+  if (lane == kWave - 1) {
+    t.tmp[wave] = incl;
+    t.tmp[kDlWaves + wave] = inclq;
+  }
+  __syncthreads();
+  const int before = lane & (kDlWaves - 1);  // totals of the waves before
+  const int ex0 = row_first_sum(lane < wave ? t.tmp[before] : 0) + incl - v0 - v1;
+  const int P0 = row_first_sum(lane < wave ? t.tmp[kDlWaves + before] : 0) + inclq - q[0] - q[1];
+  if (j0 < nblk) t.cnt[j0] = ex0;
+  if (j1 < nblk) t.cnt[j1] = ex0 + v0;
+  if (writes) {
+    if (j0 < nblk) a.block_off[j0] = ex0;
+    if (j1 < nblk) a.block_off[j1] = ex0 + v0;
+    if (j1 == nblk || j0 == nblk) a.block_off[nblk] = ex0 + (j0 == nblk ? 0 : v0);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int j = 2 * tid + u;
+    if (j < total) {
+      const int P = u ? P0 + q[0] : P0;
+      t.hr[j] = (blk[u] >= 0 ? t.cnt[blk[u]] : 0) - P;
+      t.q[j] = P + q[u];
+    }
+  }
+  __syncthreads();
+  return true;
+}
+
+// P of an expert's first column j0 (clamped: a CSR that is not a plan of this
+// group cannot send the read outside the tables).
+__device__ __forceinline__ int share_before(const int32_t *cum, int j0, int ncol) {
+  j0 = min(max(j0, 0), ncol);
+  return j0 > 0 ? cum[j0 - 1] : 0;
+}
+
+// Stable ordinals of a wave's slots, their instance and rows.  wh: per expert,
+// P of its first column plus the ordinal that the wave starts at.
+__device__ __forceinline__ void write_rows(const DlArgs &a, const int32_t (&ev)[kSteps], int64_t s0,
+                                           int32_t *wh, const int32_t *hp, const int32_t *cum,
+                                           const int32_t *base) {
+  const int lane = lane_id();
+  for (int s = 0; s < kSteps; ++s) {
+    const int64_t i = s0 + s * kWave + lane;
+    const int32_t e = ev[s];
+    const bool valid = e >= 0 && e < a.E;
+    const uint64_t act = ballot(valid);
+    if (act == 0) {
+      if (i < a.V) a.row_of_slot[i] = -1;
+      continue;
+    }
+    const uint64_t m = match_any(static_cast<uint32_t>(valid ? e : 0), a.nbits, act);
+    int row = -1;
+    if (valid) {
+      const int below = popc_below(m);
+      const int at = wh[e] + below;
+      if (below == 0) wh[e] += __popcll(m);
+      // entry range of e, clamped to the tables (a CSR that is not a plan
+      // of this group cannot send the search outside them); bisected, since
+      // a hot expert has up to R entries
+      const int j1 = min(max(hp[e + 1], 0), a.ncol);
+      int j = min(max(hp[e], 0), j1), n = j1 - j;
+      while (n > 0) {
+        const int half = n >> 1;
+        const bool up = cum[j + half] <= at;
+        j = up ? j + half + 1 : j;
+        n = up ? n - half - 1 : half;
+      }
+      if (j < j1) row = base[j] + at;
+      // a plan row that does not match these ids can point past the buffer
+      if (row < 0 || row >= a.V) {
+        row = -1;
+        report(a.status, ULTRAEP_EDATA);
+      }
+    }
+    if (i < a.V) a.row_of_slot[i] = row;
+  }
+}
+
 __global__ void __launch_bounds__(kDlThreads) k_dl_hist(DlArgs a) {
   extern __shared__ int32_t lds[];
   const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
@@ -118,81 +296,22 @@ __global__ void __launch_bounds__(kDlThreads) k_dl_hist(DlArgs a) {
     return;
   }
   // ---- layout workgroup: block sizes, offsets, entry lookup tables ----
-  // Every input is requested at once (indices clamped into range, no branch
-  // between the loads) and staged in LDS: the CSR start pointers and, per
-  // CSR column, the host rank, its slot and this rank's share.
-  const int ncol = a.ncol;
-  int32_t *cnt = lds;                  // [R*S]
-  int32_t *tmp = lds + kMaxBlocks;     // [kDlWaves]
-  int32_t *l_hp = tmp + kDlWaves;      // [E + 1]
-  int32_t *l_hr = l_hp + E + 1;        // [ncol]
-  int32_t *l_hs = l_hr + ncol;         // [ncol]
-  int32_t *l_q = l_hs + ncol;          // [ncol]
-  int vhp[kLutIters], vhr[kLutIters], vhs[kLutIters], vq[kLutIters];
-#pragma unroll
-  for (int u = 0; u < kLutIters; ++u) {
-    if (u * kDlThreads <= E) vhp[u] = a.hp[min(u * kDlThreads + tid, E)];
-    if (u * kDlThreads < ncol) {
-      const int j = min(u * kDlThreads + tid, ncol - 1);
-      vhr[u] = a.hr[j];
-      vhs[u] = a.hs[j];
-      vq[u] = a.q[j];
-    }
-  }
-  const int nblk = a.R * a.S;
-  for (int b = tid; b < nblk; b += kDlThreads) cnt[b] = 0;
-#pragma unroll
-  for (int u = 0; u < kLutIters; ++u) {
-    const int i = u * kDlThreads + tid;
-    if (i <= E) l_hp[i] = vhp[u];
-    if (i < ncol) {
-      l_hr[i] = vhr[u];
-      l_hs[i] = vhs[u];
-      l_q[i] = vq[u];
-    }
-  }
+  DlInputs in;
+  in.load(a);
+  const DlTables t = carve_tables(lds, E, a.ncol);
+  for (int b = tid; b < a.R * a.S; b += kDlThreads) t.cnt[b] = 0;
+  in.stage(a, t);
   __syncthreads();
-  // the CSR must start at 0, never decrease and end within the columns,
-  // so every entry index below is inside the tables
-  const int total = l_hp[E];
-  bool bad = l_hp[0] != 0 || total < E || total > ncol;
-  for (int e = tid; e < E; e += kDlThreads) bad |= l_hp[e] > l_hp[e + 1];
-  if (__syncthreads_or(bad)) {  // not a plan of this group
+  if (!build_tables(a, t, true)) {  // not a plan of this group
     if (tid == 0) report(a.status, ULTRAEP_EDATA);
     return;
   }
-  for (int j = tid; j < total; j += kDlThreads) {
-    const int t = l_hr[j], p = l_hs[j];
-    if (t >= 0 && t < a.R && p >= 0 && p < a.S) cnt[t * a.S + p] = l_q[j];
-    else report(a.status, ULTRAEP_EDATA);
+  for (int j = tid; j < t.hp[E]; j += kDlThreads) {
+    a.ws.ent_base[j] = t.hr[j];
+    a.ws.ent_cum[j] = t.q[j];
   }
-  __syncthreads();
-  // exclusive scan of cnt (two elements per thread) into int64 offsets
-  const int b0 = 2 * tid, b1 = 2 * tid + 1;
-  const int v0 = b0 < nblk ? cnt[b0] : 0, v1 = b1 < nblk ? cnt[b1] : 0;
-  const int incl = wave_scan_incl(v0 + v1);
-  if (lane == kWave - 1) tmp[wave] = incl;
-  __syncthreads();
-  const int wtot = lane < wave ? tmp[lane & (kDlWaves - 1)] : 0;  // totals of the waves before
-  const int ex0 = row_first_sum(wtot) + incl - v0 - v1;
-  // reuse cnt as offsets
-  if (b0 < nblk) cnt[b0] = ex0;
-  if (b1 < nblk) cnt[b1] = ex0 + v0;
-  if (b0 < nblk) a.block_off[b0] = ex0;
-  if (b1 < nblk) a.block_off[b1] = ex0 + v0;
-  if (b1 == nblk || b0 == nblk) a.block_off[nblk] = ex0 + (b0 == nblk ? 0 : v0);
-  __syncthreads();
-  for (int e = tid; e < E; e += kDlThreads) {
-    int C = 0;
-    for (int j = l_hp[e]; j < l_hp[e + 1]; ++j) {
-      const int t = l_hr[j], p = l_hs[j];
-      const bool ok = t >= 0 && t < a.R && p >= 0 && p < a.S;
-      a.ws.ent_base[j] = (ok ? cnt[t * a.S + p] : 0) - C;
-      C += l_q[j];
-      a.ws.ent_cum[j] = C;
-    }
-    a.ws.exp_tot[e] = C;
-  }
+  for (int e = tid; e < E; e += kDlThreads)
+    a.ws.exp_tot[e] = share_before(t.q, t.hp[e + 1], a.ncol) - share_before(t.q, t.hp[e], a.ncol);
 }
 
 __global__ void __launch_bounds__(kDlThreads) k_dl_rows(DlArgs a) {
@@ -294,6 +413,7 @@ __global__ void __launch_bounds__(kDlThreads) k_dl_rows(DlArgs a) {
       if (run != exp_tot) report(a.status, ULTRAEP_EDATA);
       run = 0;
     }
+    run += share_before(l_cum, l_hp[tid], ncol);
 #pragma unroll
     for (int i = 0; i < kDlWaves; ++i) w[i] = whist[i * E + tid];
 #pragma unroll
@@ -304,35 +424,7 @@ __global__ void __launch_bounds__(kDlThreads) k_dl_rows(DlArgs a) {
   }
   __syncthreads();
   // pass 2: stable ordinals, instance lookup, rows
-  for (int s = 0; s < kSteps; ++s) {
-    const int64_t i = s0 + s * kWave + lane;
-    const int32_t e = ev[s];
-    const bool valid = e >= 0 && e < E;
-    const uint64_t act = ballot(valid);
-    if (act == 0) {
-      if (i < a.V) a.row_of_slot[i] = -1;
-      continue;
-    }
-    const uint64_t m = match_any(static_cast<uint32_t>(valid ? e : 0), a.nbits, act);
-    int row = -1;
-    if (valid) {
-      const int below = popc_below(m);
-      const int ord = wh[e] + below;
-      if (below == 0) wh[e] += __popcll(m);
-      // entry range of e, clamped to the tables (a CSR that is not a plan
-      // of this group cannot send the search outside them)
-      const int j1 = min(max(l_hp[e + 1], 0), a.ncol);
-      int j = min(max(l_hp[e], 0), j1);
-      while (j < j1 && l_cum[j] <= ord) ++j;
-      if (j < j1) row = l_base[j] + ord;
-      // a plan row that does not match these ids can point past the buffer
-      if (row < 0 || row >= a.V) {
-        row = -1;
-        report(a.status, ULTRAEP_EDATA);
-      }
-    }
-    if (i < a.V) a.row_of_slot[i] = row;
-  }
+  write_rows(a, ev, s0, wh, l_hp, l_cum, l_base);
 }
 
 hipError_t launch_dispatch_layout(const int32_t *topk, int64_t V, int32_t rank,
@@ -366,8 +458,7 @@ hipError_t launch_dispatch_layout(const int32_t *topk, int64_t V, int32_t rank,
   a.status = status;
   a.stage_lut = 0;
   const size_t lds_hist = sizeof(int32_t) * kDlWaves * g.E;
-  const size_t lds_lay =
-      sizeof(int32_t) * (kMaxBlocks + kDlWaves + g.E + 1 + 3 * static_cast<size_t>(a.ncol));
+  const size_t lds_lay = sizeof(int32_t) * static_cast<size_t>(lut_ints(g.E, a.ncol));
   hipLaunchKernelGGL(k_dl_hist, dim3(ws.n_chunks + 1), dim3(kDlThreads),
                      lds_hist > lds_lay ? lds_hist : lds_lay, stream, a);
   hipError_t err = hipGetLastError();
