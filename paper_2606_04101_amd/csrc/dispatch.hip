@@ -1,7 +1,7 @@
 // Step 3 — token-to-replica assignment and dispatch permutation of one
 // source rank (Sec. 5.2 Token Assignment), then the bf16 row scatter.
 //
-// Layout (two launches, integer only):
+// Layout (integer only; two launches, or k_dl_one for few chunks):
 //   k_dl_hist  : workgroup c < n_chunks counts the expert ids of slots
 //                [c*2048, (c+1)*2048); the last workgroup turns row `rank` of
 //                the reroute split into block sizes (t, p), their exclusive
@@ -46,6 +46,8 @@ constexpr int kSumFirst = 4;   // chunk histograms per thread in the first loads
 constexpr int kSumBatch = 12;  // and in each further batch
 static_assert(kLutIters * kDlThreads >= 1024 + 256 && kLutIters * kDlThreads >= 1024 + 1,
               "the lookup tables fit the staging loops");
+constexpr int kOneChunks = 10;  // chunks up to which one launch makes the layout
+constexpr int kOneBatch = 8;    // ids of earlier chunks in flight per thread
 constexpr int kSteps = kSlotsPerWave / kWave;  // 64-slot steps per wave
 
 size_t dispatch_ws_bytes(int64_t V, int32_t E, int32_t ncol) {
@@ -427,6 +429,79 @@ __global__ void __launch_bounds__(kDlThreads) k_dl_rows(DlArgs a) {
   write_rows(a, ev, s0, wh, l_hp, l_cum, l_base);
 }
 
+// The whole layout in one launch, for few chunks: every workgroup builds the
+// tables for itself and counts the ids of the chunks before it, which costs
+// less than a second launch and the tables' way through memory.
+__global__ void __launch_bounds__(kDlThreads) k_dl_one(DlArgs a) {
+  extern __shared__ int32_t lds[];
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+  const int E = a.E, c = blockIdx.x;
+  int32_t *whist = lds;               // [kDlWaves][E]
+  int32_t *prev = lds + kDlWaves * E; // [E] ids of the chunks before
+  const DlTables t = carve_tables(prev + E, E, a.ncol);
+  DlInputs in;
+  in.load(a);
+  const int64_t s0 = static_cast<int64_t>(c) * kDispatchChunk + wave * kSlotsPerWave;
+  int32_t ev[kSteps], pv[kOneBatch];
+#pragma unroll
+  for (int s = 0; s < kSteps; ++s) ev[s] = a.topk[min(s0 + s * kWave + lane, a.V - 1)];
+  const int n_prev = c * kDispatchChunk;  // all below V
+  if (n_prev > 0) {
+#pragma unroll
+    for (int u = 0; u < kOneBatch; ++u) pv[u] = a.topk[min(u * kDlThreads + tid, n_prev - 1)];
+  }
+  for (int i = tid; i < (kDlWaves + 1) * E; i += kDlThreads) whist[i] = 0;
+  for (int b = tid; b < a.R * a.S; b += kDlThreads) t.cnt[b] = 0;
+  in.stage(a, t);
+  __syncthreads();
+  int32_t *wh = whist + wave * E;
+  bool bad = false;
+#pragma unroll
+  for (int s = 0; s < kSteps; ++s) {
+    if (s0 + s * kWave + lane >= a.V) ev[s] = -1;
+    const int32_t e = ev[s];
+    if (e >= 0 && e < E) atomicAdd(wh + e, 1);
+    bad |= e < -1 || e >= E;
+  }
+  if (bad) report(a.status, ULTRAEP_EDATA);
+  for (int i0 = 0; i0 < n_prev;) {
+#pragma unroll
+    for (int u = 0; u < kOneBatch; ++u)
+      if (i0 + u * kDlThreads + tid < n_prev && pv[u] >= 0 && pv[u] < E) atomicAdd(prev + pv[u], 1);
+    i0 += kOneBatch * kDlThreads;
+    if (i0 < n_prev) {
+#pragma unroll
+      for (int u = 0; u < kOneBatch; ++u) pv[u] = a.topk[min(i0 + u * kDlThreads + tid, n_prev - 1)];
+    }
+  }
+  if (!build_tables(a, t, c == 0)) {  // not a plan of this group
+    if (tid == 0) report(a.status, ULTRAEP_EDATA);
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+      const int64_t i = s0 + s * kWave + lane;
+      if (i < a.V) a.row_of_slot[i] = -1;
+    }
+    return;
+  }
+  if (tid < E) {
+    int run = prev[tid], w[kDlWaves];
+    const int before = share_before(t.q, t.hp[tid], a.ncol);
+#pragma unroll
+    for (int i = 0; i < kDlWaves; ++i) w[i] = whist[i * E + tid];
+#pragma unroll
+    for (int i = 0; i < kDlWaves; ++i) {
+      whist[i * E + tid] = before + run;
+      run += w[i];
+    }
+    // the last workgroup has counted every id: the shares have to add up to them
+    if (c + 1 == static_cast<int>(gridDim.x) &&
+        run != share_before(t.q, t.hp[tid + 1], a.ncol) - before)
+      report(a.status, ULTRAEP_EDATA);
+  }
+  __syncthreads();
+  write_rows(a, ev, s0, wh, t.hp, t.q, t.hr);
+}
+
 hipError_t launch_dispatch_layout(const int32_t *topk, int64_t V, int32_t rank,
                                   const ultraep_group &g,
                                   const ultraep_plan_buf &plan,
@@ -457,6 +532,17 @@ hipError_t launch_dispatch_layout(const int32_t *topk, int64_t V, int32_t rank,
   a.ws = ws;
   a.status = status;
   a.stage_lut = 0;
+  // One launch for up to 10 chunks.  Two launches / one, graph of 20 calls: 1
+  // chunk of E = 128 8.9 / 6.2 us, 4 chunks 8.9 / 6.9, 8 chunks 9.1 / 7.9, 16
+  // chunks 9.1 / 9.7 (R = 64); 8 chunks of E = 8 9.8 / 8.8, 12 chunks 9.8 / 10.4;
+  // 12 chunks of E = 64 with eight hot experts 8.9 / 9.6.  Equal ids collide in
+  // the counts, so with fewer than 10 experts one chunk each.
+  const size_t lds_one = sizeof(int32_t) * ((kDlWaves + 1) * static_cast<size_t>(g.E) +
+                                            static_cast<size_t>(lut_ints(g.E, a.ncol)));
+  if (ws.n_chunks > 0 && ws.n_chunks <= (g.E < kOneChunks ? g.E : kOneChunks) && lds_one <= 64 * 1024) {
+    hipLaunchKernelGGL(k_dl_one, dim3(ws.n_chunks), dim3(kDlThreads), lds_one, stream, a);
+    return hipGetLastError();
+  }
   const size_t lds_hist = sizeof(int32_t) * kDlWaves * g.E;
   const size_t lds_lay = sizeof(int32_t) * static_cast<size_t>(lut_ints(g.E, a.ncol));
   hipLaunchKernelGGL(k_dl_hist, dim3(ws.n_chunks + 1), dim3(kDlThreads),

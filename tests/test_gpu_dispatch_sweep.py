@@ -169,3 +169,32 @@ def test_layout_chunk_sums(R, E, T):
     osend, oros, ooff, ost = oracle.dispatch(x, tk[rank], rank, og, op)
     assert np.array_equal(ros, oros) and np.array_equal(off, ooff)
     assert np.array_equal(send, osend)
+
+
+# one launch up to 10 chunks of 2048 slots (fewer with less than 10 experts, two
+# launches when the tables do not fit LDS), around each edge
+@pytest.mark.parametrize("R,E,NS", [(1, 2, 0), (2, 6, 1), (64, 64, 4), (64, 128, 2), (32, 512, 8), (16, 1024, 2)])
+@pytest.mark.parametrize("V", [1, 2047, 2048, 2049, 3 * 2048, 10 * 2048 - 1, 10 * 2048, 10 * 2048 + 1])
+def test_layout_one_launch(R, E, NS, V):
+    rng = np.random.default_rng(V + E)
+    tk = np.minimum(rng.geometric(min(1.0, 6 / E), (R, V, 1)) - 1, E - 1).astype(np.int32)
+    tk[rng.random(tk.shape) < 0.1] = -1
+    g, og = gp.groups(R, E, NS, 1)
+    load, _ = oracle.count(tk, E, R)
+    op = oracle.plan(load, og)
+    plan = gp.gpu_plan(load, g)
+    x = (np.arange(V * 8) & 0xFFFF).astype(np.uint16).reshape(V, 8)
+    for rank in {0, R - 1}:
+        send, ros, off, st = gp.gpu_dispatch(x, tk[rank], rank, g, plan)
+        assert st == 0
+        osend, oros, ooff, ost = oracle.dispatch(x, tk[rank], rank, og, op)
+        assert np.array_equal(ros, oros) and np.array_equal(off, ooff)
+        assert np.array_equal(send, osend)
+    # ids out of range, ids that the shares do not match, host lists of no group
+    bad = tk[0].copy()
+    bad[V // 2, 0] = E
+    assert gp.gpu_dispatch(x, bad, 0, g, plan)[3] == uep.ULTRAEP_EDATA
+    bad[V // 2, 0] = -1 if tk[0][V // 2, 0] >= 0 else 0
+    assert gp.gpu_dispatch(x, bad, 0, g, plan)[3] == uep.ULTRAEP_EDATA
+    plan.host_ptr[E] = E + R * NS + 1
+    assert gp.gpu_dispatch(x, tk[0], 0, g, plan)[3] == uep.ULTRAEP_EDATA
