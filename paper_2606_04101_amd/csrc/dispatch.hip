@@ -539,7 +539,15 @@ hipError_t launch_dispatch_layout(const int32_t *topk, int64_t V, int32_t rank,
   // the counts, so with fewer than 10 experts one chunk each.
   const size_t lds_one = sizeof(int32_t) * ((kDlWaves + 1) * static_cast<size_t>(g.E) +
                                             static_cast<size_t>(lut_ints(g.E, a.ncol)));
-  if (ws.n_chunks > 0 && ws.n_chunks <= (g.E < kOneChunks ? g.E : kOneChunks) && lds_one <= 64 * 1024) {
+  // Rows written over the ids (row_of_slot == topk) take two launches unless
+  // one workgroup does it all: k_dl_one reads the ids of earlier chunks, which
+  // their workgroups may have overwritten by then; k_dl_hist has read them all
+  // before k_dl_rows, whose workgroups read their own chunk's and then write it.
+  const uintptr_t ids = reinterpret_cast<uintptr_t>(topk), out = reinterpret_cast<uintptr_t>(row_of_slot);
+  const uintptr_t span = static_cast<uintptr_t>(V) * sizeof(int32_t);
+  const bool apart = ids + span <= out || out + span <= ids;
+  if (ws.n_chunks > 0 && ws.n_chunks <= (g.E < kOneChunks ? g.E : kOneChunks) &&
+      (apart || ws.n_chunks == 1) && lds_one <= 64 * 1024) {
     hipLaunchKernelGGL(k_dl_one, dim3(ws.n_chunks), dim3(kDlThreads), lds_one, stream, a);
     return hipGetLastError();
   }

@@ -198,3 +198,28 @@ def test_layout_one_launch(R, E, NS, V):
     assert gp.gpu_dispatch(x, bad, 0, g, plan)[3] == uep.ULTRAEP_EDATA
     plan.host_ptr[E] = E + R * NS + 1
     assert gp.gpu_dispatch(x, tk[0], 0, g, plan)[3] == uep.ULTRAEP_EDATA
+
+
+@pytest.mark.parametrize("V", [700, 2048, 2049, 5 * 2048 + 3, 10 * 2048, 12 * 2048])
+def test_layout_in_place(V):
+    """row_of_slot may be the ids' own memory: every id is read before a row
+    takes its place, at one chunk of 2048 slots, at several and past the one
+    launch."""
+    R, E, NS = 8, 64, 2
+    rng = np.random.default_rng(V)
+    tk = np.minimum(rng.geometric(0.1, (R, V, 1)) - 1, E - 1).astype(np.int32)
+    tk[rng.random(tk.shape) < 0.1] = -1
+    g, og = gp.groups(R, E, NS, 1)
+    load, _ = oracle.count(tk, E, R)
+    plan = gp.gpu_plan(load, g)
+    ids = gp.dev_i32(tk[3])
+    off = torch.empty(R * g.S + 1, dtype=torch.int64, device=gp.DEV)
+    ws = torch.empty(uep.ultraep_dispatch_ws_bytes(V, 1, g), dtype=torch.uint8, device=gp.DEV)
+    st = gp.zero_status()
+    uep.ultraep_dispatch_layout(ids, V, 1, 3, g, plan, ids, off, ws, st)
+    torch.cuda.synchronize()
+    assert int(st.item()) == 0
+    x = np.zeros((V, 8), np.uint16)
+    _, oros, ooff, _ = oracle.dispatch(x, tk[3], 3, og, oracle.plan(load, og))
+    assert np.array_equal(ids.cpu().numpy().reshape(-1), oros.reshape(-1))
+    assert np.array_equal(off.cpu().numpy(), ooff)
