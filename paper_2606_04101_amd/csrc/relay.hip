@@ -131,8 +131,10 @@ __global__ void __launch_bounds__(kRlThreads) k_relay(RlArgs a) {
         const int e = s_x[t * NS + s - nm];
         ok = e >= 0 && e < E && e / nm != t;
         if (ok) {
+          // (the pointers are not known to be sound here: j0 >= 0 keeps j - 1
+          // inside the columns)
           const int j0 = s_hp[e];
-          ok = j > j0 && j < s_hp[e + 1] && (j == j0 + 1 || t > s_hr[j - 1]);
+          ok = j0 >= 0 && j > j0 && j < s_hp[e + 1] && (j == j0 + 1 || t > s_hr[j - 1]);
         }
       }
       bad |= !ok;

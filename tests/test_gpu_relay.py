@@ -123,7 +123,7 @@ def test_relay_edges_of_the_staging(seed, R, E, NS, n_hot, threshold):
 
 
 @pytest.mark.parametrize("what", ["ptr_start", "ptr_descends", "ptr_long", "ptr_past", "ptr_wraps",
-                                  "home_rank", "home_slot", "home_twice", "lists_swapped", "rank_twice",
+                                  "ptr_negative", "home_rank", "home_slot", "home_twice", "lists_swapped", "rank_twice",
                                   "slot_range", "rank_range", "on_home"])
 def test_relay_refuses_broken_host_lists(what):
     """One fault each in otherwise sound lists: EDATA, outputs untouched."""
@@ -145,6 +145,8 @@ def test_relay_refuses_broken_host_lists(what):
         hp[E] = g.E + R * NS + 1
     elif what == "ptr_wraps":
         hp[a] = -2 ** 31
+    elif what == "ptr_negative":  # and the first column holds a replica of that expert
+        hr[0], hs[0], hp[a] = hr[ja + 1], hs[ja + 1], -5
     elif what == "home_rank":
         hr[ja] = (hr[ja] + 1) % R
     elif what == "home_slot":
