@@ -36,6 +36,20 @@ PyObject *s_c, *s_ws, *s_cuda_stream;     // attribute names
 struct Args {
   PyObject *const *a;
   bool ok = true;
+  // What the call uses beyond its arguments (a Plan's descriptor and its
+  // workspace), held until the call has been enqueued: another thread may give
+  // the Plan other ones while the interpreter lock is released.
+  PyObject *held[2];
+  int n_held = 0;
+
+  explicit Args(PyObject *const *argv) : a(argv) {}
+  Args(const Args &) = delete;
+  Args &operator=(const Args &) = delete;
+  ~Args() {
+    for (int i = 0; i < n_held; ++i) Py_DECREF(held[i]);
+  }
+  // takes over a new reference
+  PyObject *hold(PyObject *o) { return held[n_held++] = o; }
 
   PyObject *fail() {
     ok = false;
@@ -92,10 +106,9 @@ struct Args {
   const ultraep_plan_buf *plan(int i) {
     if (!ok || reinterpret_cast<PyObject *>(Py_TYPE(a[i])) != t_plan) return fail(), nullptr;
     PyObject *c = attr(a[i], s_c);
-    auto *p = c ? static_cast<const ultraep_plan_buf *>(structure(c, t_buf, sizeof(ultraep_plan_buf)))
-                : nullptr;
-    Py_XDECREF(c);  // the Plan holds it
-    return p;
+    if (!c) return nullptr;
+    return static_cast<const ultraep_plan_buf *>(
+        structure(hold(c), t_buf, sizeof(ultraep_plan_buf)));
   }
   // a workspace tensor (None: the plan's own) and its bytes
   void *workspace(int i, int plan_arg, size_t &bytes) {
@@ -104,17 +117,13 @@ struct Args {
     PyObject *o = a[i];
     if (o == Py_None) {
       if (plan_arg < 0 || !(o = attr(a[plan_arg], s_ws))) return fail();
-    } else {
-      Py_INCREF(o);
+      if (hold(o) == Py_None) return fail();
     }
-    void *p = nullptr;
-    if (o == Py_None) fail();
-    else p = tensor(o, 0, 0);
+    void *p = tensor(o, 0, 0);
     if (ok) {
       const at::Tensor &t = THPVariable_Unpack(o);
       bytes = static_cast<size_t>(t.numel()) * t.element_size();
     }
-    Py_DECREF(o);  // the argument or the Plan holds it
     return p;
   }
   // torch's current stream for None, a torch stream, or an address

@@ -4,6 +4,9 @@ and the same errors, over the argument forms the binding accepts (positional
 and keyword, bf16 and int16 tensors, streams as None, torch streams and
 addresses, other integer types).  Needs an MI355X."""
 import ctypes
+import gc
+import sys
+import weakref
 
 import numpy as np
 import pytest
@@ -138,3 +141,55 @@ def test_other_argument_types():
         uep.ultraep_plan(load, uep.Group(R, E, NS, 1), plan, ws=plan.ws[:16])
     torch.cuda.synchronize()
     assert counts[1].item() == 8
+
+
+@pytest.fixture
+def bound_to():
+    """Binds the native half to a Python function in place of one entry point
+    (nothing is enqueued), and back to the library afterwards."""
+    n = uep._load_native()
+    def bind(name, fn):
+        n.bind({name: ctypes.cast(fn, ctypes.c_void_p).value}, uep.Group, uep.Plan, uep.PlanBuf)
+        return n
+    yield bind
+    uep._load_native()
+
+
+def test_native_half_holds_what_a_call_uses(bound_to):
+    """A Plan that is given another descriptor and workspace during a call (by
+    another thread, the interpreter lock being released) keeps those the call
+    was made with until it returns, and not longer."""
+    g = uep.Group(R, E, NS, 1)
+    plan = uep.Plan(g, gp.DEV)
+    refs = weakref.ref(plan.c), weakref.ref(plan.ws)
+    seen = []
+
+    @ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p,
+                      ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p)
+    def entry(load, group, buf, ws, ws_bytes, stream):
+        plan.c = plan.ws = None
+        gc.collect()
+        seen.append([r() is not None for r in refs])
+        return 0
+
+    n = bound_to("ultraep_plan", entry)
+    load = torch.zeros(R, E, dtype=torch.int32, device=gp.DEV)
+    assert n.plan(load, g, plan, None, None) == 0
+    assert seen == [[True, True]]
+    gc.collect()
+    assert [r() for r in refs] == [None, None]
+
+
+def test_native_half_keeps_no_reference_of_a_call_it_declines():
+    """Among them a workspace whose memory may not be written."""
+    g = uep.Group(R, E, NS, 1)
+    plan = uep.Plan(g, gp.DEV)
+    load = torch.zeros(R, E, dtype=torch.int32, device=gp.DEV)
+    torch._C._set_throw_on_mutable_data_ptr(plan.ws)
+    n, ws, c = uep._load_native(), plan.ws, plan.c
+    before = sys.getrefcount(ws), sys.getrefcount(c)
+    for _ in range(5):
+        assert n.plan(load, g, plan, None, None) is None
+        assert n.plan(load, g, plan, ws, None) is None
+        assert n.plan(load[:-1], g, plan, None, None) is None
+    assert (sys.getrefcount(ws), sys.getrefcount(c)) == before
