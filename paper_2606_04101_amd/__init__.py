@@ -8,8 +8,9 @@ kernels.  Before a call it checks that every tensor is large enough for the
 shapes given, so a kernel never runs past a caller's buffer.  A call whose
 arguments pass the checks goes through ``_native.so`` (``csrc/binding.cpp``),
 which makes them in C++; one that it does not take (None is returned) is
-checked, and refused or made, by the ctypes code below.  A missing library
-raises immediately; there is no fallback path.
+checked, and refused or made, by the ctypes code below, and so is every call
+where ``_native.so`` is not built for this torch.  A missing library raises
+immediately; there is no fallback for the kernels.
 
 Reference: "UltraEP: Unleash MoE Training and Inference on Rack-Scale Nodes
 with Near-Optimal Load Balancing", arXiv 2606.04101 (Algorithm 1, Sec. 5-6).
@@ -120,22 +121,38 @@ def lib():
     return _lib
 
 
-def _load_native():
-    """The native half of the binding, bound to the library's entry points."""
-    global _native
-    path = os.path.join(_HERE, "_native.so")
-    if not os.path.exists(path):
-        raise RuntimeError(f"{path} is not built; run __graft_entry__.build() first")
-    import importlib
+class _Declines:
+    """In place of the native half where there is none: it takes no call, so
+    every call goes through the ctypes code."""
 
-    import torch  # noqa: F401  (the module links against torch's libraries)
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _load_native():
+    """The native half of the binding, bound to the library's entry points; a
+    stand-in that takes no call, and a warning, where it is not built or was
+    built for another torch (the calls then cost more host time, 5-8 us each)."""
+    global _native
     L = lib()
-    m = importlib.import_module("._native", __name__)
-    m.bind({f"ultraep_{n}": ctypes.cast(getattr(L, f"ultraep_{n}"), _P).value
-            for n in ("count", "plan", "plan_noalloc", "plan_replicate", "plan_reroute",
-                      "dispatch", "dispatch_layout", "dispatch_scatter", "pack_replicas",
-                      "reroute_and_pack", "relay_plan", "pack_relay", "combine",
-                      "grad_reduce")}, Group, Plan, PlanBuf)
+    try:
+        import importlib
+
+        import torch  # the module links against torch's libraries
+        m = importlib.import_module("._native", __name__)
+        if m.torch_version != str(torch.__version__):
+            raise ImportError(f"it was built for torch {m.torch_version}")
+    except (ImportError, AttributeError) as e:
+        import warnings
+        warnings.warn(f"{__name__}: calls go through ctypes, the native half of the binding "
+                      f"does not load: {e}", RuntimeWarning, stacklevel=3)
+        m = _Declines()
+    else:
+        m.bind({f"ultraep_{n}": ctypes.cast(getattr(L, f"ultraep_{n}"), _P).value
+                for n in ("count", "plan", "plan_noalloc", "plan_replicate", "plan_reroute",
+                          "dispatch", "dispatch_layout", "dispatch_scatter", "pack_replicas",
+                          "reroute_and_pack", "relay_plan", "pack_relay", "combine",
+                          "grad_reduce")}, Group, Plan, PlanBuf)
     _native = m
     return m
 

@@ -401,5 +401,12 @@ PyMODINIT_FUNC PyInit__native() {
   s_c = PyUnicode_InternFromString("c");
   s_ws = PyUnicode_InternFromString("ws");
   s_cuda_stream = PyUnicode_InternFromString("cuda_stream");
-  return s_c && s_ws && s_cuda_stream ? PyModule_Create(&module) : nullptr;
+  if (!s_c || !s_ws || !s_cuda_stream) return nullptr;
+  PyObject *m = PyModule_Create(&module);
+  // torch's C++ interface differs between versions: the Python half checks this
+  if (m && PyModule_AddStringConstant(m, "torch_version", TORCH_BUILD) != 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
 }

@@ -1,6 +1,11 @@
 """The Python binding refuses tensors too small (or of the wrong element size)
 for the shapes it is given, before the library is called, so that no kernel
 runs past a caller's buffer.  No GPU needed: the check comes first."""
+import os
+import shutil
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -98,3 +103,72 @@ def test_native_half_declines_host_tensors():
     assert n.count(t(40)) is None
     assert n.plan(t(64), G, object(), None, 0) is None
     assert n.plan(t(64), (4, 16, 2, 8), None, None, 0) is None
+
+
+@pytest.mark.parametrize("native", ["missing", "no_library", "other_torch"])
+def test_calls_without_the_native_half(native, tmp_path):
+    """Where _native.so is absent or does not fit, calls go through ctypes:
+    the same refusals, from the binding's checks and from the library."""
+    src = os.path.dirname(uep.__file__)
+    pkg = tmp_path / "paper_2606_04101_amd"
+    pkg.mkdir()
+    for f in ("__init__.py", "_build.py", "libultraep.so"):
+        shutil.copy(os.path.join(src, f), pkg / f)
+    if native == "no_library":
+        (pkg / "_native.so").write_text("not a library")
+    elif native == "other_torch":
+        shutil.copy(os.path.join(src, "_native.so"), pkg / "_native.so")
+    code = f"""
+import sys, warnings
+sys.path.insert(0, {str(tmp_path)!r})
+import torch
+import paper_2606_04101_amd as uep
+if {native!r} == "other_torch":
+    torch.__version__ = "0.1"
+with warnings.catch_warnings(record=True) as w:
+    warnings.simplefilter("always")
+    for _ in range(2):
+        try:
+            uep.ultraep_dispatch_scatter(None, 0, 1, 7, None, None, None, stream=0)
+        except uep.UltraEPError as e:
+            assert e.code == uep.ULTRAEP_EINVAL
+        else:
+            raise AssertionError("not refused")
+    try:
+        uep.ultraep_count(torch.zeros(39, dtype=torch.int32), 10, 2, 16, 2, None, None, stream=0)
+    except ValueError as e:
+        assert "topk" in str(e)
+    else:
+        raise AssertionError("not refused")
+assert [v.category for v in w if "ctypes" in str(v.message)] == [RuntimeWarning]
+"""
+    env = {k: v for k, v in os.environ.items() if k != "ULTRAEP_LIB"}
+    r = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, env=env, timeout=300,
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_library_builds_without_the_native_half(monkeypatch, tmp_path):
+    """A torch without headers, or no host compiler: the library is built all
+    the same, and no file of an earlier build is left to be loaded with it."""
+    from paper_2606_04101_amd import _build
+    for name in ("LIB", "NATIVE"):
+        monkeypatch.setattr(_build, name, str(tmp_path / os.path.basename(getattr(_build, name))))
+    stale = tmp_path / "_native.so"
+    stale.write_text("earlier build")
+
+    def fails():
+        raise RuntimeError("no headers")
+    done = []
+
+    def run(cmd, **kw):
+        done.append(cmd)
+        open(cmd[cmd.index("-o") + 1], "w").close()
+        return subprocess.CompletedProcess(cmd, 0, "", "")
+    monkeypatch.setattr(_build, "build_native", fails)
+    monkeypatch.setattr(_build.subprocess, "run", run)
+    monkeypatch.setattr(_build, "HERE", str(tmp_path))
+    with pytest.warns(RuntimeWarning, match="no headers"):
+        assert _build.build() == str(tmp_path / "libultraep.so")
+    assert len(done) == len(_build.SOURCES) + 1
+    assert (tmp_path / "libultraep.so").exists() and not stale.exists()
