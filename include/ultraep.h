@@ -46,7 +46,8 @@
  * E <= 1024, 0 <= n_slot, R * n_slot <= 256, u_min >= 1,
  * 1 <= beta_den <= beta_num <= 2^20, 1 <= k <= min(E, 64), T >= 0,
  * T * k < 2^31, H % 8 == 0, W % 8 == 0, 16-byte aligned x / send / w_main /
- * staging.  The total load of a plan must not exceed 2^30 tokens (device
+ * staging; other buffers aligned to their elements unless their call asks for
+ * more, workspaces to 8 bytes (not checked).  The total load of a plan must not exceed 2^30 tokens (device
  * status ULTRAEP_EDATA otherwise).
  */
 #ifndef ULTRAEP_H

@@ -55,11 +55,15 @@ constexpr int kBitWords = (kNodes + 63) / 64;  // outcome bits per round
 constexpr int kCopies = 8;
 static_assert(kHdr <= kHdrSpan && kBitWords * 8 == 128, "outcome copies are whole lines");
 
+// The workspace is 8-byte aligned (its 64-bit words and atomics need that), so
+// its 16-byte entries are declared with that alignment: still one load each.
+typedef v4i v4i_ws __attribute__((aligned(8)));
+
 struct PlanWs {
   int64_t *hdr;    // [4] tau_lo0, tau_hi0, L, status, then per round j the
                    // bisection state after rounds 0..j: lo, hi, best, probes
   uint64_t *bits;  // [kRounds][kCopies][kBitWords] feasible probes, one bit per node
-  v4i *rank;       // [kMaxR] i-th rank of the visiting order (descending load):
+  v4i_ws *rank;    // [kMaxR] i-th rank of the visiting order (descending load):
                    // its load and its largest expert load; i-th rank of the
                    // target order (ascending load): rank and load; 0 past R
   uint2 *ent;      // [E] (load, expert) in visiting order: rank by rank, each
@@ -69,6 +73,9 @@ struct PlanWs {
   int32_t *res;    // [kRounds][kNodes] probe outcome
   uint32_t *rec;   // [kRounds][kNodes][2 * RS] (e | t << 16, delta) pairs
 };
+
+static_assert(alignof(v4i_ws) == 8 && alignof(uint2) <= 8 && alignof(uint64_t) <= 8,
+              "no part of the workspace asks for more than 8 bytes");
 
 constexpr int64_t even(int64_t n) { return (n + 1) / 2 * 2; }
 
@@ -85,7 +92,7 @@ static PlanWs carve(void *ws, int32_t R, int32_t E, int32_t NS) {
   PlanWs w;
   w.hdr = static_cast<int64_t *>(ws);
   w.bits = reinterpret_cast<uint64_t *>(w.hdr + kHdrSpan);
-  w.rank = reinterpret_cast<v4i *>(w.bits + kRounds * kCopies * kBitWords);
+  w.rank = reinterpret_cast<v4i_ws *>(w.bits + kRounds * kCopies * kBitWords);
   w.ent = reinterpret_cast<uint2 *>(w.rank + kMaxR);
   int32_t *p = reinterpret_cast<int32_t *>(w.ent + E);
   w.ell = p;

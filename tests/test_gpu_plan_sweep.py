@@ -14,6 +14,7 @@ pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
     import gpu_path as gp
+    import paper_2606_04101_amd as uep
 
 
 def sweep_case(seed):
@@ -82,3 +83,22 @@ def test_plan_probe_edges(R, E, NS):
         assert op.status == oracle.OK
         gp.assert_plan_equal(gp.gpu_plan(load, g), op)
         gp.assert_plan_equal(gp.gpu_plan(load, g, split=True), op)
+
+
+@pytest.mark.parametrize("R,E,NS,scale", [(4, 16, 2, 300), (64, 1024, 4, 2000), (5, 640, 1, 160000)])
+def test_plan_workspace_of_eight_byte_alignment(R, E, NS, scale):
+    """The workspace need only be 8-byte aligned, with records in one and in
+    several slots and loads past the packing limit."""
+    rng = np.random.default_rng(R)
+    load = (rng.dirichlet(np.full(E, 0.5), R) * E * scale).astype(np.int32)
+    g, og = gp.groups(R, E, NS, 3)
+    op = oracle.plan(load, og)
+    assert op.status == oracle.OK
+    plan = uep.Plan(g, gp.DEV)
+    n = uep.ultraep_plan_ws_bytes(g)
+    room = torch.full((n + 16,), 0xA5, dtype=torch.uint8, device=gp.DEV)
+    start = (8 - room.data_ptr()) % 16
+    uep.ultraep_plan(gp.dev_i32(load), g, plan, ws=room[start:start + n])
+    torch.cuda.synchronize()
+    gp.assert_plan_equal(plan, op)
+    assert (room[:start] == 0xA5).all() and (room[start + n:] == 0xA5).all()
