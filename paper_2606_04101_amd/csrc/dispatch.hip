@@ -36,7 +36,6 @@ namespace uep {
 constexpr int kDlThreads = 1024;
 constexpr int kDlWaves = kDlThreads / kWave;
 constexpr int kSlotsPerWave = kDispatchChunk / kDlWaves;  // 128
-constexpr int kMaxBlocks = 2048;                           // R * S
 
 static_assert(kSlotsPerWave % kWave == 0, "chunk must split into wave steps");
 // CSR columns (E + R * n_slot <= 1024 + 256) and start pointers (E + 1) per
@@ -48,6 +47,7 @@ static_assert(kLutIters * kDlThreads >= 1024 + 256 && kLutIters * kDlThreads >= 
               "the lookup tables fit the staging loops");
 constexpr int kOneChunks = 10;  // chunks up to which one launch makes the layout
 constexpr int kOneBatch = 8;    // ids of earlier chunks in flight per thread
+constexpr int kOneCopies = 8;   // counts of them at most, dealt over the lanes
 constexpr int kSteps = kSlotsPerWave / kWave;  // 64-slot steps per wave
 
 size_t dispatch_ws_bytes(int64_t V, int32_t E, int32_t ncol) {
@@ -76,6 +76,7 @@ struct DlArgs {
   int32_t rank, R, E, NS, nm, S, ncol, nbits;
   int32_t parts, div_E;  // threads per expert in the sums over chunks, 2^20 / E rounded up
   int32_t stage_lut;  // copy host_ptr / entry tables into LDS
+  int32_t copies;     // k_dl_one: counts of the earlier ids, a power of two
   const int32_t *hp, *hr, *hs, *q;  // q = reroute row of `rank`
   int32_t *row_of_slot;
   int64_t *block_off;
@@ -89,7 +90,7 @@ static_assert(kDlWaves == 16, "the waves' totals fill one row of lanes");
 
 // This rank's layout tables in LDS.
 struct DlTables {
-  int32_t *cnt;  // [kMaxBlocks] rows per (rank, slot) block, then its first row
+  int32_t *cnt;  // [ncol = R * S] rows per (rank, slot) block, then its first row
   int32_t *tmp;  // [2 * kDlWaves]
   int32_t *hp;   // [E + 1]
   int32_t *hr;   // [ncol] host rank, then the entry's first row minus P
@@ -98,13 +99,19 @@ struct DlTables {
 };
 
 __host__ __device__ __forceinline__ int lut_ints(int E, int ncol) {
-  return kMaxBlocks + 2 * kDlWaves + E + 1 + 3 * ncol;
+  return 2 * kDlWaves + E + 1 + 4 * ncol;
+}
+
+// Clears n 32-bit words of LDS (n a multiple of 4, p 16-byte aligned).
+__device__ __forceinline__ void clear_lds(int32_t *p, int n) {
+  v4i *v = reinterpret_cast<v4i *>(p);
+  for (int i = threadIdx.x; i < n / 4; i += kDlThreads) v[i] = v4i{0, 0, 0, 0};
 }
 
 __device__ __forceinline__ DlTables carve_tables(int32_t *p, int E, int ncol) {
   DlTables t;
   t.cnt = p;
-  t.tmp = t.cnt + kMaxBlocks;
+  t.tmp = t.cnt + ncol;
   t.hp = t.tmp + 2 * kDlWaves;
   t.hr = t.hp + E + 1;
   t.hs = t.hr + ncol;
@@ -160,8 +167,7 @@ __device__ __forceinline__ bool build_tables(const DlArgs &a, const DlTables &t,
   bool bad = t.hp[0] != 0 || total < E || total > ncol;
   for (int e = tid; e < E; e += kDlThreads) bad |= t.hp[e] > t.hp[e + 1];
   if (__syncthreads_or(bad)) return false;
-  static_assert(2 * kDlThreads >= kMaxBlocks && 2 * kDlThreads >= 1024 + 256,
-                "two blocks and two columns per thread");
+  static_assert(2 * kDlThreads >= 1024 + 256, "two blocks and two columns per thread");
   const int j0 = 2 * tid, j1 = 2 * tid + 1;
   int blk[2], q[2];
 #pragma unroll
@@ -429,16 +435,26 @@ __global__ void __launch_bounds__(kDlThreads) k_dl_rows(DlArgs a) {
   write_rows(a, ev, s0, wh, l_hp, l_cum, l_base);
 }
 
+// LDS words of k_dl_one's copies of the earlier ids' counts.
+__host__ __device__ __forceinline__ int prev_ints(int copies, int E) {
+  return (copies * (E | 1) + 3) / 4 * 4;
+}
+
 // The whole layout in one launch, for few chunks: every workgroup builds the
 // tables for itself and counts the ids of the chunks before it, which costs
-// less than a second launch and the tables' way through memory.
+// less than a second launch and the tables' way through memory.  Equal ids of a
+// wave add to one LDS address one after another, so the counts of the earlier
+// ids are kept in several copies, lane by lane, in different banks: with every
+// id the same expert, 10 chunks of E = 64 take 10.4 us (23.5 with one count).
 __global__ void __launch_bounds__(kDlThreads) k_dl_one(DlArgs a) {
-  extern __shared__ int32_t lds[];
+  extern __shared__ __attribute__((aligned(16))) int32_t lds[];
   const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
   const int E = a.E, c = blockIdx.x;
-  int32_t *whist = lds;               // [kDlWaves][E]
-  int32_t *prev = lds + kDlWaves * E; // [E] ids of the chunks before
-  const DlTables t = carve_tables(prev + E, E, a.ncol);
+  const int stride = E | 1;            // the copies of an expert's count in different banks
+  int32_t *whist = lds;                // [kDlWaves][E]
+  int32_t *prev = lds + kDlWaves * E;  // [copies][stride] ids of the chunks before
+  const int n_cnt = prev_ints(a.copies, E);
+  const DlTables t = carve_tables(prev + n_cnt, E, a.ncol);
   DlInputs in;
   in.load(a);
   const int64_t s0 = static_cast<int64_t>(c) * kDispatchChunk + wave * kSlotsPerWave;
@@ -450,7 +466,7 @@ __global__ void __launch_bounds__(kDlThreads) k_dl_one(DlArgs a) {
 #pragma unroll
     for (int u = 0; u < kOneBatch; ++u) pv[u] = a.topk[min(u * kDlThreads + tid, n_prev - 1)];
   }
-  for (int i = tid; i < (kDlWaves + 1) * E; i += kDlThreads) whist[i] = 0;
+  clear_lds(whist, kDlWaves * E + (n_prev > 0 ? n_cnt : 0));
   for (int b = tid; b < a.R * a.S; b += kDlThreads) t.cnt[b] = 0;
   in.stage(a, t);
   __syncthreads();
@@ -464,10 +480,11 @@ __global__ void __launch_bounds__(kDlThreads) k_dl_one(DlArgs a) {
     bad |= e < -1 || e >= E;
   }
   if (bad) report(a.status, ULTRAEP_EDATA);
+  int32_t *mine = prev + (lane & (a.copies - 1)) * stride;
   for (int i0 = 0; i0 < n_prev;) {
 #pragma unroll
     for (int u = 0; u < kOneBatch; ++u)
-      if (i0 + u * kDlThreads + tid < n_prev && pv[u] >= 0 && pv[u] < E) atomicAdd(prev + pv[u], 1);
+      if (i0 + u * kDlThreads + tid < n_prev && pv[u] >= 0 && pv[u] < E) atomicAdd(mine + pv[u], 1);
     i0 += kOneBatch * kDlThreads;
     if (i0 < n_prev) {
 #pragma unroll
@@ -484,7 +501,14 @@ __global__ void __launch_bounds__(kDlThreads) k_dl_one(DlArgs a) {
     return;
   }
   if (tid < E) {
-    int run = prev[tid], w[kDlWaves];
+    int run = 0, w[kDlWaves];
+    if (n_prev > 0) {
+#pragma unroll
+      for (int p = 0; p < kOneCopies; ++p) {
+        const int v = prev[min(p, a.copies - 1) * stride + tid];
+        run += p < a.copies ? v : 0;
+      }
+    }
     const int before = share_before(t.q, t.hp[tid], a.ncol);
 #pragma unroll
     for (int i = 0; i < kDlWaves; ++i) w[i] = whist[i * E + tid];
@@ -532,13 +556,21 @@ hipError_t launch_dispatch_layout(const int32_t *topk, int64_t V, int32_t rank,
   a.ws = ws;
   a.status = status;
   a.stage_lut = 0;
-  // One launch for up to 10 chunks.  Two launches / one, graph of 20 calls: 1
-  // chunk of E = 128 8.9 / 6.2 us, 4 chunks 8.9 / 6.9, 8 chunks 9.1 / 7.9, 16
-  // chunks 9.1 / 9.7 (R = 64); 8 chunks of E = 8 9.8 / 8.8, 12 chunks 9.8 / 10.4;
-  // 12 chunks of E = 64 with eight hot experts 8.9 / 9.6.  Equal ids collide in
-  // the counts, so with fewer than 10 experts one chunk each.
-  const size_t lds_one = sizeof(int32_t) * ((kDlWaves + 1) * static_cast<size_t>(g.E) +
-                                            static_cast<size_t>(lut_ints(g.E, a.ncol)));
+  // One launch for up to 10 chunks.  Two launches / one, graph of 20 calls, ids
+  // spread over E = 128 (R = 64): 1 chunk 8.7 / 6.0 us, 4 chunks 8.8 / 6.9, 10
+  // chunks 9.0 / 8.2, 16 chunks 9.0 / 9.0; two experts alone: 4 chunks 10.0 /
+  // 8.5, 10 chunks 10.1 / 10.3, 12 chunks 10.2 / 10.7; one expert alone: 8 chunks
+  // 10.9 / 10.3, 10 chunks 10.8 / 11.0, 12 chunks 10.8 / 11.4.  The same line at
+  // E = 8, 256 and 512.  Where LDS does not hold all the copies of the counts, a
+  // hot expert's chunks cost more: E = 640, four copies, one expert alone: 5
+  // chunks 11.8 / 11.2, 6 chunks 11.9 / 12.0, 8 chunks 11.9 / 12.6.
+  a.copies = kOneCopies;
+  const auto lds_for = [&](int copies) {
+    return sizeof(int32_t) * static_cast<size_t>(kDlWaves * g.E + prev_ints(copies, g.E) +
+                                                 lut_ints(g.E, a.ncol));
+  };
+  while (a.copies > 1 && lds_for(a.copies) > 64 * 1024) a.copies /= 2;
+  const size_t lds_one = lds_for(a.copies);
   // Rows written over the ids (row_of_slot == topk) take two launches unless
   // one workgroup does it all: k_dl_one reads the ids of earlier chunks, which
   // their workgroups may have overwritten by then; k_dl_hist has read them all
@@ -546,7 +578,8 @@ hipError_t launch_dispatch_layout(const int32_t *topk, int64_t V, int32_t rank,
   const uintptr_t ids = reinterpret_cast<uintptr_t>(topk), out = reinterpret_cast<uintptr_t>(row_of_slot);
   const uintptr_t span = static_cast<uintptr_t>(V) * sizeof(int32_t);
   const bool apart = ids + span <= out || out + span <= ids;
-  if (ws.n_chunks > 0 && ws.n_chunks <= (g.E < kOneChunks ? g.E : kOneChunks) &&
+  const int64_t most = a.copies == kOneCopies ? kOneChunks : 2 + a.copies;
+  if (ws.n_chunks > 0 && ws.n_chunks <= most &&
       (apart || ws.n_chunks == 1) && lds_one <= 64 * 1024) {
     hipLaunchKernelGGL(k_dl_one, dim3(ws.n_chunks), dim3(kDlThreads), lds_one, stream, a);
     return hipGetLastError();

@@ -223,3 +223,23 @@ def test_layout_in_place(V):
     _, oros, ooff, _ = oracle.dispatch(x, tk[3], 3, og, oracle.plan(load, og))
     assert np.array_equal(ids.cpu().numpy().reshape(-1), oros.reshape(-1))
     assert np.array_equal(off.cpu().numpy(), ooff)
+
+
+# the one launch's counts in 8, 4, 2 and 1 copies (as many as LDS holds), up to
+# the chunks that each takes and past them, half of the ids one expert
+@pytest.mark.parametrize("R,E,NS", [(64, 512, 4), (64, 640, 1), (64, 640, 4), (64, 704, 1)])
+@pytest.mark.parametrize("V", [2 * 2048 + 65, 3 * 2048, 4 * 2048, 6 * 2048, 6 * 2048 + 1])
+def test_layout_copies_of_the_counts(R, E, NS, V):
+    rng = np.random.default_rng(V + E + NS)
+    tk = rng.integers(-1, E, (R, V, 1)).astype(np.int32)
+    tk[rng.random(tk.shape) < 0.5] = E // 3
+    g, og = gp.groups(R, E, NS, 7)
+    load, _ = oracle.count(tk, E, R)
+    op = oracle.plan(load, og)
+    plan = gp.gpu_plan(load, g)
+    x = (np.arange(V * 8) & 0xFFFF).astype(np.uint16).reshape(V, 8)
+    send, ros, off, st = gp.gpu_dispatch(x, tk[1], 1, g, plan)
+    assert st == 0
+    osend, oros, ooff, ost = oracle.dispatch(x, tk[1], 1, og, op)
+    assert np.array_equal(ros, oros) and np.array_equal(off, ooff)
+    assert np.array_equal(send, osend)
