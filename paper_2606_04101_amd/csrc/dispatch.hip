@@ -8,16 +8,16 @@
 //                prefix block_off, and per CSR entry the running share over
 //                all columns and the first row minus the entry's start in it.
 //   k_dl_rows  : workgroup c sums the histograms of chunks < c (its base
-//                ordinal per expert; all threads share the chunks, and the
-//                loads past the first four per thread are skipped when
-//                there are no such chunks: code that runs once costs its
-//                fetch), then each wave ranks its 128 slots
+//                ordinal per expert; up to 16 threads share the chunks, and the
+//                loads past the first four and past the first eight per
+//                thread are skipped when there are no such chunks: code
+//                that runs once costs its fetch), then each wave ranks its 128 slots
 //                stably with ballot matches (wave-private running counts in
 //                LDS, scanned across waves), bisects for the first
 //                instance whose running share exceeds the ordinal and writes
 //                the row.
-//   Both kernels (graph of 20 calls, one rank of R = 64): 9.3 us for 32768 slots
-//   of E = 256 and 10.4 us for 131072; 10.1 and 11.2 us with the shares of an
+//   Both kernels (graph of 20 calls, one rank of R = 64): 9.2 us for 32768 slots
+//   of E = 256 and 10.2 us for 131072; 10.1 and 11.2 us with the shares of an
 //   expert summed by one thread and its instances searched one by one, and 13.0
 //   for the latter with the sums over chunks in one thread per expert too.
 // Scatter (bandwidth bound): persistent waves walk the tokens; a wave holds
@@ -41,8 +41,10 @@ static_assert(kSlotsPerWave % kWave == 0, "chunk must split into wave steps");
 // CSR columns (E + R * n_slot <= 1024 + 256) and start pointers (E + 1) per
 // thread when a 1024-thread workgroup stages them
 constexpr int kLutIters = 2;
-constexpr int kSumFirst = 4;   // chunk histograms per thread in the first loads
-constexpr int kSumBatch = 12;  // and in each further batch
+constexpr int kSumFirst = 4;   // chunk histograms per thread in the first loads,
+constexpr int kSumSecond = 4;  // in the second ones
+constexpr int kSumBatch = 12;  // and in a batch (the second ones and more)
+constexpr int kSumParts = 16;  // threads that share an expert's chunks at most
 static_assert(kLutIters * kDlThreads >= 1024 + 256 && kLutIters * kDlThreads >= 1024 + 1,
               "the lookup tables fit the staging loops");
 constexpr int kOneChunks = 10;  // chunks up to which one launch makes the layout
@@ -344,13 +346,21 @@ __global__ void __launch_bounds__(kDlThreads) k_dl_rows(DlArgs a) {
   const int nsum = c == 0 ? static_cast<int>(a.ws.n_chunks) : c;
   const int32_t *h = a.ws.hist + e_t;
   const bool many = nsum > kSumFirst * parts;  // else the other loads are skipped
-  int hv[kSumFirst], hw[kSumBatch];
+  const bool more = nsum > (kSumFirst + kSumSecond) * parts;
+  int hv[kSumFirst] = {}, hw[kSumBatch] = {};
+  if (part < parts) {
 #pragma unroll
-  for (int u = 0; u < kSumFirst; ++u) hv[u] = h[min(part + u * parts, nsum - 1) * E];
-  if (many) {
+    for (int u = 0; u < kSumFirst; ++u) hv[u] = h[min(part + u * parts, nsum - 1) * E];
+  }
+  if (many && part < parts) {
 #pragma unroll
-    for (int u = 0; u < kSumBatch; ++u)
+    for (int u = 0; u < kSumSecond; ++u)
       hw[u] = h[min(part + (kSumFirst + u) * parts, nsum - 1) * static_cast<int64_t>(E)];
+    if (more) {
+#pragma unroll
+      for (int u = kSumSecond; u < kSumBatch; ++u)
+        hw[u] = h[min(part + (kSumFirst + u) * parts, nsum - 1) * static_cast<int64_t>(E)];
+    }
   }
   const int exp_tot = c == 0 ? a.ws.exp_tot[e_t] : 0;
   int vhp[kLutIters], vcum[kLutIters], vbase[kLutIters];
@@ -393,21 +403,27 @@ __global__ void __launch_bounds__(kDlThreads) k_dl_rows(DlArgs a) {
     l_base = p + E + 1 + ncol;
   }
   // sums over the chunks (further batches of loads when there are more than
-  // kSumBatch chunks per thread)
+  // kSumFirst + kSumBatch chunks per thread)
   {
     int s = 0;
 #pragma unroll
     for (int u = 0; u < kSumFirst; ++u) s += part + u * parts < nsum ? hv[u] : 0;
-    if (many) {
+    if (many && part < parts) {
       int c0 = part + kSumFirst * parts;
-      for (;;) {
 #pragma unroll
-        for (int u = 0; u < kSumBatch; ++u) s += c0 + u * parts < nsum ? hw[u] : 0;
-        c0 += kSumBatch * parts;
-        if (c0 - part >= nsum) break;
+      for (int u = 0; u < kSumSecond; ++u) s += c0 + u * parts < nsum ? hw[u] : 0;
+      if (more) {
+        int u0 = kSumSecond;
+        for (;;) {
 #pragma unroll
-        for (int u = 0; u < kSumBatch; ++u)
-          hw[u] = h[min(c0 + u * parts, nsum - 1) * static_cast<int64_t>(E)];
+          for (int u = 0; u < kSumBatch; ++u) s += u >= u0 && c0 + u * parts < nsum ? hw[u] : 0;
+          u0 = 0;
+          c0 += kSumBatch * parts;
+          if (c0 - part >= nsum) break;
+#pragma unroll
+          for (int u = 0; u < kSumBatch; ++u)
+            hw[u] = h[min(c0 + u * parts, nsum - 1) * static_cast<int64_t>(E)];
+        }
       }
     }
     psum[tid] = s;
@@ -545,7 +561,9 @@ hipError_t launch_dispatch_layout(const int32_t *topk, int64_t V, int32_t rank,
   a.nbits = bits_for(g.E);
   // tid * div_E >> 20 is tid / E for tid < 1024: the excess of the product
   // over tid * 2^20 / E is below tid, so below 2^20 / E
-  a.parts = kDlThreads / g.E;
+  // few enough that adding up an expert's partial sums stays short (E = 1, 16
+  // chunks: 19.4 us for the layout with 1024 parts, 8.6 with 16)
+  a.parts = kDlThreads / g.E < kSumParts ? kDlThreads / g.E : kSumParts;
   a.div_E = ((1 << 20) + g.E - 1) / g.E;
   a.hp = plan.host_ptr;
   a.hr = plan.host_rank;

@@ -243,3 +243,23 @@ def test_layout_copies_of_the_counts(R, E, NS, V):
     osend, oros, ooff, ost = oracle.dispatch(x, tk[1], 1, og, op)
     assert np.array_equal(ros, oros) and np.array_equal(off, ooff)
     assert np.array_equal(send, osend)
+
+
+# the sums over chunk histograms where few threads share them (16 of E = 1, 9
+# and 64, one of E = 600 with threads left over) and around their batches
+# of 4, 4 and 12 loads per thread
+@pytest.mark.parametrize("R,E", [(1, 1), (3, 9), (16, 64), (8, 600)])
+@pytest.mark.parametrize("chunks", [11, 16 * 4 + 1, 16 * 8 + 1, 16 * 16 + 3])
+def test_layout_chunk_sum_batches(R, E, chunks):
+    V = chunks * 2048 - 77
+    rng = np.random.default_rng(chunks + E)
+    tk = rng.integers(-1, E, (V, 1)).astype(np.int32)
+    load = np.tile(np.bincount(tk[tk >= 0], minlength=E).astype(np.int32), (R, 1))
+    g, og = gp.groups(R, E, 1, 50)
+    plan, op = gp.gpu_plan(load, g), oracle.plan(load, og)
+    x = (np.arange(V * 8) & 0xFFFF).astype(np.uint16).reshape(V, 8)
+    send, ros, off, st = gp.gpu_dispatch(x, tk, R - 1, g, plan)
+    assert st == 0
+    osend, oros, ooff, ost = oracle.dispatch(x, tk, R - 1, og, op)
+    assert np.array_equal(ros, oros) and np.array_equal(off, ooff)
+    assert np.array_equal(send, osend)
