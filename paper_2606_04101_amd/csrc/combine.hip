@@ -20,7 +20,12 @@
 // registers from group to group: 3001 tokens of k = 12, H = 4104 (300 MB)
 // take 52.7 us (5.7 TB/s), against 82.8 us (3.6 TB/s) with one row's load in
 // flight at a time.  Groups of 4 or 6 rows, groups of equal size, and 12 or 16
-// rows together measured the same or up to 15 % slower.
+// rows together measured the same or up to 15 % slower.  Where a call has few
+// units or a row is short, latency and instructions bound it instead: there the
+// loads take no branch (bounds-checked buffer loads, so a masked row reads
+// nothing and counts as +0 times +0).  With a branch around each load the
+// one-chunk kernel waits for a load before it issues the next one: 300 tokens of
+// k = 16, H = 512 took 10.0 us, now 5.7 (8.7 with one row in flight).
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -34,6 +39,9 @@ constexpr int kCbGrid = 65535;
 constexpr int kCbRows = 8;  // rows loaded together per chunk
 constexpr int kCbChunks = 2;       // k <= kCbRows: 16-byte chunks per lane per step
 constexpr int kCbLaneChunks = 2;   //               and per lane per work unit
+// dword 3 of a raw buffer resource (32-bit data format), non-temporal loads
+constexpr uint32_t kRawBufferWord3 = 0x00020000u;
+constexpr int kLoadNt = 2;
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
@@ -129,8 +137,11 @@ k_combine(const v4u *__restrict__ y, int64_t n_rows, const float *__restrict__ g
 
 // k > kCbRows: up to kCh 16-byte chunks per lane of one token's row, `per`
 // chunks in all (nblk equal units per row); the loads of kCbRows rows are in
-// flight together, then those of the next group.
-template <int kCh>
+// flight together, then those of the next group.  kFew: loads without a branch
+// (a resource per row; chunks from c_end on, and all of a masked row's, are out
+// of its bounds and load as 0), and only the rows past k are left out of the
+// sums: a masked row adds gate 0 times 0, which changes no sum (none is -0).
+template <int kCh, bool kFew>
 __global__ void __launch_bounds__(kCbThreads)
 k_combine_many(const v4u *__restrict__ y, int64_t n_rows, const float *__restrict__ gate,
                const int32_t *__restrict__ row_of_slot, int64_t T, int32_t k, int32_t nch,
@@ -145,26 +156,40 @@ k_combine_many(const v4u *__restrict__ y, int64_t n_rows, const float *__restric
     int row;
     float g;
     token_rows(row_of_slot, gate, t, k, lane, n_rows, status, row, g);
+    if (kFew && row < 0) g = 0.f;
     const int c0 = b * per + lane, c_end = min(nch, (b + 1) * per);
+    // (uniform, and known to be: a resource in scalar registers)
+    const uint32_t bytes = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(c_end)) * 16u;
     float acc[kCh][8] = {};
     for (int k0 = 0; k0 < k; k0 += kCbRows) {
       v4u v[kCh][kCbRows];
 #pragma unroll
       for (int kk = 0; kk < kCbRows; ++kk) {
-        const int r = k0 + kk < k ? readlane(row, k0 + kk) : -1;
+        // k <= 64, so the lane read is in the wave; lanes past k hold -1
+        const int r = kFew || k0 + kk < k ? readlane(row, k0 + kk) : -1;
+        if constexpr (kFew) {
+          const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+              const_cast<v4u *>(y) + static_cast<int64_t>(max(r, 0)) * nch, 0,
+              r < 0 ? 0u : bytes, kRawBufferWord3);
 #pragma unroll
-        for (int u = 0; u < kCh; ++u) {
-          const int cc = c0 + u * kWave;
-          if (r >= 0 && cc < c_end)
-            v[u][kk] = __builtin_nontemporal_load(y + static_cast<int64_t>(r) * nch + cc);
+          for (int u = 0; u < kCh; ++u)
+            v[u][kk] = __builtin_amdgcn_raw_buffer_load_b128(
+                rs, static_cast<uint32_t>(c0 + u * kWave) * 16u, 0, kLoadNt);
+        } else {
+#pragma unroll
+          for (int u = 0; u < kCh; ++u) {
+            const int cc = c0 + u * kWave;
+            if (r >= 0 && cc < c_end)
+              v[u][kk] = __builtin_nontemporal_load(y + static_cast<int64_t>(r) * nch + cc);
+          }
         }
       }
 #pragma unroll
       for (int u = 0; u < kCh; ++u) {
 #pragma unroll
         for (int kk = 0; kk < kCbRows; ++kk) {
-          const int r = k0 + kk < k ? readlane(row, k0 + kk) : -1;
-          if (r >= 0 && c0 + u * kWave < c_end)
+          const int r = k0 + kk < k ? (kFew ? 0 : readlane(row, k0 + kk)) : -1;
+          if (r >= 0 && (kFew || c0 + u * kWave < c_end))
             acc_chunk(acc[u], __int_as_float(readlane(__float_as_int(g), k0 + kk)), v[u][kk]);
         }
       }
@@ -182,7 +207,7 @@ static dim3 combine_grid(int64_t units) {
   return dim3(static_cast<unsigned>(need < kCbGrid ? need : kCbGrid));
 }
 
-template <int kCh>
+template <int kCh, bool kFew>
 static void start_many(const v4u *y, int64_t n_rows, const float *gate, const int32_t *row_of_slot,
                        int64_t T, int32_t k, int32_t nch, v4u *out, int32_t *status,
                        hipStream_t stream) {
@@ -190,7 +215,7 @@ static void start_many(const v4u *y, int64_t n_rows, const float *gate, const in
   // unit's width leaves no nearly empty wave; in whole 128-byte lines
   const int32_t nblk = (nch + kCh * kWave - 1) / (kCh * kWave);
   const int32_t per = ((nch + nblk - 1) / nblk + 7) / 8 * 8;
-  hipLaunchKernelGGL(k_combine_many<kCh>, combine_grid(T * nblk), dim3(kCbThreads), 0, stream, y,
+  hipLaunchKernelGGL((k_combine_many<kCh, kFew>), combine_grid(T * nblk), dim3(kCbThreads), 0, stream, y,
                      n_rows, gate, row_of_slot, T, k, nch, nblk, per, out, status);
 }
 
@@ -205,17 +230,29 @@ hipError_t launch_combine(const uint16_t *y, int64_t n_rows, const float *gate,
   // (fewer partly filled waves).  Measured, one / two chunks, T = 3001 rows of
   // k = 12: H = 7168 85.8 / 89.1 us, 4096 50.0 / 51.2, 5608 70.1 / 71.8; but
   // 4104 (89 % filled) 55.3 / 52.7, 2880 (94 %) 39.4 / 37.0, and 520 (51 %,
-  // T = 16000) 46.4 / 40.5.
+  // T = 16000) 46.4 / 40.5.  Rows of one chunk per lane, and calls of few
+  // units, load without branches.  Measured over rotating buffers, with one row
+  // in flight / one or two chunks as above / without branches: H = 256, k = 10,
+  // T = 1 3.7 / 4.5 / 3.4 us, T = 300 6.3 / 5.3 / 4.6, T = 16000 24.5 / 25.9 /
+  // 21.6; T = 33, H = 1024, k = 12 7.9 / 8.2 / 5.3; T = 300, H = 4096, k = 12
+  // (2400 units) 55.9 / 10.7 / 8.6; with full rows of one chunk (H = 512, k = 12)
+  // T = 300 7.2 / 8.0 / 5.4 and T = 3001 13.8 / 11.2 / 9.4.  Above the lines the
+  // rest is ahead by up to 4 % (H = 4096, k = 12, T = 3001 53.5 / 55.7; H = 7168,
+  // k = 9, T = 300 10.8 / 11.2).  One row in flight stays ahead where a row is a
+  // few lanes and tokens are many (H = 8, k = 9, T = 16000 12.5 / 23.1 / 15.4).
   const int64_t ones = (nch + kWave - 1) / kWave;
+  const bool full = 20 * static_cast<int64_t>(nch) >= 19 * kWave * ones;
   if (k <= kCbRows)
     hipLaunchKernelGGL(k_combine,
                        combine_grid(T * ((nch + kCbLaneChunks * kWave - 1) / (kCbLaneChunks * kWave))),
                        dim3(kCbThreads), 0, stream, ys, n_rows, gate, row_of_slot, T, k, nch, os,
                        status);
-  else if (20 * static_cast<int64_t>(nch) >= 19 * kWave * ones)
-    start_many<1>(ys, n_rows, gate, row_of_slot, T, k, nch, os, status, stream);
+  else if (T * ones <= (ones == 1 ? 6000 : 2400) || (ones == 1 && !full))
+    start_many<1, true>(ys, n_rows, gate, row_of_slot, T, k, nch, os, status, stream);
+  else if (full)
+    start_many<1, false>(ys, n_rows, gate, row_of_slot, T, k, nch, os, status, stream);
   else
-    start_many<2>(ys, n_rows, gate, row_of_slot, T, k, nch, os, status, stream);
+    start_many<2, false>(ys, n_rows, gate, row_of_slot, T, k, nch, os, status, stream);
   return hipGetLastError();
 }
 

@@ -117,6 +117,43 @@ def test_combine_many_rows_per_token(k, H):
     check_combine(y, gate, ros)
 
 
+# more than 8 rows per token on both sides of the line between small and large
+# calls (2400 one-chunk units, 6000 of rows that are one chunk), with full, 95 %, 94 % and nearly empty last units
+@pytest.mark.parametrize("T,H", [(1200, 1024), (1201, 1024), (1201, 968), (1201, 960),
+                                 (800, 1032), (801, 1032), (6000, 488), (6001, 488),
+                                 (6001, 480)])
+@pytest.mark.parametrize("k", [9, 17])
+def test_combine_many_rows_few_and_many_units(T, k, H):
+    rng = np.random.default_rng(T + k + H)
+    n_rows = T * k
+    y = bf16_normals(rng, (n_rows, H))
+    gate = softmax_gates(rng, T, k)
+    ros = rng.permutation(n_rows).astype(np.int32)
+    ros[rng.random(n_rows) < 0.15] = -1
+    check_combine(y, gate, ros.reshape(T, k))
+
+
+@pytest.mark.parametrize("T,H", [(300, 64), (1201, 1032)])
+def test_combine_many_rows_special_values(T, H):
+    """Special rows and gates with more than 8 rows per token, and masked slots
+    whose gates are infinities and NaN: they add nothing."""
+    rng = np.random.default_rng(T)
+    k = 11
+    specials = np.array([0x0000, 0x8000, 0x7F80, 0xFF80, 0x7FC0, 0xFFC1, 0x0001, 0x807F,
+                         0x0080, 0x7F7F, 0xFF7F, 0x3F80, 0xBF80, 0x4C00, 0xCC00], np.uint16)
+    y = np.where(rng.random((T * k, H)) < 0.1, rng.choice(specials, (T * k, H)),
+                 rng.choice(specials[-4:], (T * k, H))).astype(np.uint16)
+    y[: k * 20] &= 0x8000  # tokens of signed zeros alone
+    gate = rng.choice(np.array([1.0, -0.5, 0.0, -0.0, 2.0 ** -100, 0.25], np.float32),
+                      (T, k)).astype(np.float32)
+    ros = np.arange(T * k, dtype=np.int32).reshape(T, k)
+    masked = rng.random((T, k)) < 0.4
+    masked[7] = True
+    ros[masked] = -1
+    gate[masked] = rng.choice(np.array([np.inf, -np.inf, np.nan, -0.0, 1.0], np.float32), masked.sum())
+    check_combine(y, gate, ros)
+
+
 def test_combine_special_values():
     """Signed zeros, infinities, NaNs, subnormal rows and subnormal
     products, large values that overflow to infinity, negative gates."""
