@@ -626,29 +626,33 @@ constexpr int kScWaves = kScThreads / kWave;
 // walks tokens t, t + 2048, ...  Measured against one wave per token and
 // against 256 to 1024 workgroups on the DeepSeek-V3-shaped layer.
 constexpr int kScGrid = 512;
-constexpr int64_t kScSplit = 768;  // tokens below which rows are cut
 constexpr int64_t kScFill = 2048;  // units that fill the resident waves
+constexpr int kScWide = 16;        // 64-chunk steps of a unit of a wide row at most
 // dword 3 of a raw buffer resource (32-bit data format) and the store cache
 // policy: sc1 streams the rows out at the device scope.  Buffer stores with
 // sc1 measured 3-4 % faster than plain or non-temporal global stores.
 constexpr uint32_t kRawBufferWord3 = 0x00020000u;
 constexpr int kStoreSc1 = 16;
 
-// Stores chunk-lane values of one token (chunks c0 .. c0 + 64 U - 1) to its k
-// destination rows, one 1 KiB chunk (64 lanes x 16 B) to every row before the
-// next chunk.  Each row gets its own buffer resource (base = the row, size =
-// the row), so offsets stay 32-bit and anything past the row is dropped by
-// the hardware.
-template <int U>
+// Stores chunk-lane values of one token (chunks c0 .. c_end - 1, at most 64 U)
+// to its k destination rows, one 1 KiB chunk (64 lanes x 16 B) to every row
+// before the next chunk.  Each row gets its own buffer resource (base = the
+// row, size = the row), so offsets stay 32-bit and anything past the row is
+// dropped by the hardware.  kPlain: ordinary stores, see launch_dispatch_scatter.
+template <int U, bool kPlain>
 __device__ __forceinline__ void store_rows(const v4u (&v)[U], int rows, int k, int64_t V,
-                                           int32_t nch, int c0, int lane, v4u *send) {
+                                           int32_t nch, int c0, int c_end, int lane, v4u *send) {
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int cc = c0 + u * kWave + lane;
-    if (cc < nch) {
+    if (cc < c_end) {
       for (int kk = 0; kk < k; ++kk) {
         const int row = readlane(rows, kk);
         if (row >= 0 && row < V) {
+          if constexpr (kPlain) {
+            send[static_cast<int64_t>(row) * nch + cc] = v[u];
+            continue;
+          }
           const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
               send + static_cast<int64_t>(row) * nch, 0, static_cast<uint32_t>(nch) * 16u,
               kRawBufferWord3);
@@ -661,24 +665,27 @@ __device__ __forceinline__ void store_rows(const v4u (&v)[U], int rows, int k, i
 }
 
 // Rows of up to 64 * U chunks (H <= 8192), one unit each, or (kSplit) rows cut
-// into `pieces` units of 64 * U chunks: persistent waves, each holding one
-// unit in registers while the next one is being loaded.
+// into `pieces` units of `per` <= 64 * U chunks: persistent waves, each holding
+// one unit in registers while the next one is being loaded.
 template <int U, bool kSplit>
 __global__ void __launch_bounds__(kScThreads)
 k_scatter(const v4u *__restrict__ x, int64_t T, int32_t k, int32_t nch, int32_t pieces,
-          const int32_t *__restrict__ row_of_slot, const int64_t *n_routed,
+          int32_t per, const int32_t *__restrict__ row_of_slot, const int64_t *n_routed,
           v4u *__restrict__ send) {
+  constexpr bool kPlain = kSplit && U == kScWide;
   const int lane = lane_id();
   const int64_t V = T * k, n = kSplit ? T * pieces : T;
   const int64_t nw = static_cast<int64_t>(gridDim.x) * kScWaves;
   const int64_t gw = static_cast<int64_t>(blockIdx.x) * kScWaves + threadIdx.x / kWave;
+  const auto end_of = [&](int c0) { return kSplit ? min(nch, c0 + per) : nch; };
   const auto fetch = [&](int64_t unit, v4u(&v)[U], int &rows, int &c0) {
     const int64_t t = kSplit ? unit / pieces : unit;
-    c0 = kSplit ? static_cast<int>(unit - t * pieces) * (kWave * U) : 0;
+    c0 = kSplit ? static_cast<int>(unit - t * pieces) * per : 0;
+    const int c_end = end_of(c0);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int cc = c0 + u * kWave + lane;
-      if (cc < nch) v[u] = __builtin_nontemporal_load(x + t * nch + cc);
+      if (cc < c_end) v[u] = __builtin_nontemporal_load(x + t * nch + cc);
     }
     rows = lane < k ? row_of_slot[t * k + lane] : -1;
   };
@@ -692,7 +699,7 @@ k_scatter(const v4u *__restrict__ x, int64_t T, int32_t k, int32_t nch, int32_t 
       v4u w[U];
       int rn = -1, cn = 0;
       if (un < n) fetch(un, w, rn, cn);
-      store_rows<U>(v, rows, k, V, nch, c0, lane, send);
+      store_rows<U, kPlain>(v, rows, k, V, nch, c0, end_of(c0), lane, send);
       if (un >= n) break;
 #pragma unroll
       for (int u = 0; u < U; ++u) v[u] = w[u];
@@ -715,9 +722,12 @@ template <int U, bool kSplit>
 static void start_scatter(const v4u *x, int64_t T, int32_t k, int32_t nch, const int32_t *row_of_slot,
                           const int64_t *n_routed, v4u *send, hipStream_t stream) {
   const int32_t pieces = kSplit ? (nch + U * kWave - 1) / (U * kWave) : 1;
+  // the pieces of a wide row are equal, in whole 128-byte lines of an aligned row
+  const int32_t per = U == kScWide ? ((nch + pieces - 1) / pieces + 7) / 8 * 8 : U * kWave;
   const int64_t need = (T * pieces + kScWaves - 1) / kScWaves;
   hipLaunchKernelGGL((k_scatter<U, kSplit>), dim3(static_cast<unsigned>(need < kScGrid ? need : kScGrid)),
-                     dim3(kScThreads), 0, stream, x, T, k, nch, pieces, row_of_slot, n_routed, send);
+                     dim3(kScThreads), 0, stream, x, T, k, nch, pieces, per, row_of_slot,
+                     n_routed, send);
 }
 
 hipError_t launch_dispatch_scatter(const uint16_t *x, int64_t T, int32_t k,
@@ -730,18 +740,38 @@ hipError_t launch_dispatch_scatter(const uint16_t *x, int64_t T, int32_t k,
   v4u *sd = reinterpret_cast<v4u *>(send);
   const auto start = [&](auto f) { f(xs, T, k, nch, row_of_slot, n_routed, sd, stream); };
   // Whole rows per wave keep the stores of a row together; they are cut where
-  // that leaves waves idle or where a row does not fit the registers.  Below
-  // kScSplit tokens: the widest units that still make kScFill of them.
-  // Layout and scatter in whole rows / cut, k = 8: 64 tokens of H = 4096
-  // 16.6 / 10.7 us, 256 tokens 17.9 / 13.2, 512 tokens of H = 7168 23.7 / 20.1,
-  // but 1000 of them 31.8 / 32.4 and 1500 of H = 4096 26.8 / 27.4 (units of 256
-  // chunks).  H = 12288: 300 tokens 31.6 / 19.6 us, 4000 tokens 188.6 / 186.4
-  // against one wave per token walking the row in passes.
-  const auto fills = [&](int u) { return T * ((per_lane + u - 1) / u) >= kScFill; };
-  if (per_lane > 16 || (per_lane > 1 && T < kScSplit)) {
-    if (per_lane > 8 && fills(8)) start(start_scatter<8, true>);
-    else if (per_lane > 4 && fills(4)) start(start_scatter<4, true>);
-    else if (per_lane > 2 && fills(2)) start(start_scatter<2, true>);
+  // that leaves waves idle or where a row does not fit the registers.  Measured
+  // over rotating buffers (past the last-level cache), us.
+  // Rows of up to 16 steps of 64 chunks are cut below `whole` tokens, whole / cut,
+  // k = 8: H = 4096, 511 tokens 10.4 / 8.2, 700 11.4 / 10.9; H = 5120, 600 12.4 /
+  // 11.4, 700 12.8 / 15.6; H = 7168, 511 15.7 / 13.2, 640 16.5 / 17.4, 767 18.3 /
+  // 19.6; k = 16: H = 4096, 511 15.1 / 14.1, 700 17.6 / 18.9; H = 5120, 600 19.4 /
+  // 20.7; H = 1024, 640 6.2 / 5.6; k = 1: H = 7168, 767 9.0 / 7.9.  More rows a
+  // token keep the memory busy with fewer waves.
+  // The units are the widest that are enough: of 4 steps and more, a third over
+  // the resident waves, as a few units over them leave the second turn nearly
+  // empty (4 / 2 steps: H = 6144, k = 8, 683 tokens, 2049 / 4098 units 18.9 / 15.1;
+  // H = 5120, k = 2, 767, 2301 / 3835 8.3 / 6.5; H = 8192, k = 8, 600, 2400 / 4800
+  // 19.3 / 17.8).
+  // Wide rows take equal pieces of up to 16 steps and ordinary stores once these
+  // make two thirds of the resident waves: sc1 stores go past the L2, which
+  // otherwise joins the lines that two rows or two pieces share, and narrow rows
+  // per token write too little for sc1 to matter.  One wave per token walking the
+  // row in passes / units of 8 steps, sc1 / these: H = 12288, 1500 tokens, k = 1
+  // 17.9 / 21.1 / 15.9, k = 8 70.8 / 65.8 / 63.0; H = 9216, 1500, k = 1 14.7 / 17.1 /
+  // 13.0; rows that are no whole lines, H = 8200, 4096, k = 1 31.5 / 37.4 / 31.1,
+  // k = 8 154 / 176 / 155, k = 16, 767 55.8 / 69.3 / 59.6.  Such rows change over
+  // earlier (H = 8200, k = 8, 300 tokens, 600 units 18.3 / 15.1 / 12.4 but k = 1 8.2 /
+  // 4.8 / 5.6), where others lose (H = 12288, k = 4, 511, 1022 units 18.5 / 12.7 / 13.5).
+  const auto units = [&](int u) { return T * ((per_lane + u - 1) / u); };
+  const bool wide = per_lane > kScWide;
+  const int64_t whole = k >= 12 && per_lane > 2 ? 512 : k >= 8 && per_lane > 8 ? 640 : 768;
+  if (wide && units(kScWide) >= (nch % 8 == 0 ? 2 * kScFill / 3 : k >= 4 ? 600 : 768)) {
+    start(start_scatter<kScWide, true>);
+  } else if (wide || (per_lane > 1 && T < whole)) {
+    if (per_lane > 8 && units(8) >= kScFill * 4 / 3) start(start_scatter<8, true>);
+    else if (per_lane > 4 && units(4) >= kScFill * 4 / 3) start(start_scatter<4, true>);
+    else if (per_lane > 2 && units(2) >= kScFill) start(start_scatter<2, true>);
     else start(start_scatter<1, true>);
   } else if (per_lane <= 1) {
     start(start_scatter<1, false>);

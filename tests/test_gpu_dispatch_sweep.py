@@ -150,6 +150,31 @@ def test_scatter_units(T, k, H):
     assert np.array_equal(gp.host_u16(send), ref)
 
 
+# the lines between whole rows and cut ones, the units over and under the resident
+# waves, and wide rows in equal pieces with ordinary stores (whole lines or not,
+# one and several units per wave, a last piece of one chunk)
+@pytest.mark.parametrize("T,k,H", [
+    (511, 16, 1032), (512, 16, 1032), (639, 8, 4608), (640, 8, 4608), (767, 8, 4096), (683, 3, 6144),
+    (682, 3, 4104), (299, 4, 8200), (300, 4, 8200), (511, 12, 1032), (512, 12, 1032), (383, 2, 8200), (384, 2, 8200), (682, 2, 8704), (683, 2, 8704), (1100, 1, 8200),
+    (256, 3, 16392), (255, 3, 16392), (1367, 1, 24576)])
+def test_scatter_lines(T, k, H):
+    rng = np.random.default_rng(T + k + H)
+    V = T * k
+    x = rng.integers(0, 1 << 16, (T, H), dtype=np.uint16)
+    routed = rng.random(V) >= 0.1
+    ros = np.full(V, -1, np.int32)
+    nr = int(routed.sum())
+    ros[routed] = rng.permutation(nr)
+    room = torch.full((V + 2, H), 0x5A5A, dtype=torch.int16, device=gp.DEV)
+    uep.ultraep_dispatch_scatter(gp.dev_u16(x), T, k, H, gp.dev_i32(ros),
+                                 torch.tensor([nr], dtype=torch.int64, device=gp.DEV), room[1:-1])
+    torch.cuda.synchronize()
+    ref = np.zeros((V, H), np.uint16)
+    ref[ros[routed]] = x[np.arange(V)[routed] // k]
+    assert np.array_equal(gp.host_u16(room[1:-1].contiguous()), ref)
+    assert (room[0] == 0x5A5A).all() and (room[-1] == 0x5A5A).all()
+
+
 # the sums over chunk histograms: threads per expert from 1 to many, chunk
 # counts around the first batch of loads and over several batches
 @pytest.mark.parametrize("R,E", [(1, 1), (3, 6), (8, 128), (4, 300), (8, 1000), (16, 1024)])
