@@ -202,6 +202,8 @@ __global__ void __launch_bounds__(kRlThreads) k_relay(RlArgs a) {
         // set of the ranks of relays 0..i
         int key = act ? (s_vol[t] << 6) | t : INT32_MAX;
         fetch(min(hi + 1, nhot - 1));
+        n_relays += n;
+        if (n == fe) continue;  // one replica, the relay: no volume changes
         uint64_t set = 0;
         int C = 0, vprev = 0, l_c = 0, l_lo = 0, l_hi = 0;
         bool leaf = act;
@@ -243,7 +245,6 @@ __global__ void __launch_bounds__(kRlThreads) k_relay(RlArgs a) {
           atomicAdd(&s_vol[win], 1);
         }
         if (lane == 0) s_vol[home] -= fe - n;
-        n_relays += n;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the volumes, to the next expert
       }
     }
