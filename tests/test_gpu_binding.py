@@ -23,6 +23,31 @@ if torch.cuda.is_available():
 R, E, NS, T, k, H, W = 4, 16, 2, 65, 3, 136, 64
 
 
+# the native functions: arguments in order; a tensor as its size in elements and
+# its type, ws a workspace (its size is the library's to check)
+I32, I64, U16, F32 = (getattr(torch, t) for t in ("int32", "int64", "int16", "float32"))
+S, CAP, V = E // R + NS, 5, T * k
+TOPK, ROWS, STATUS, LOAD = (V, I32), (V, I32), (1, I32), (R * E, I32)
+PACKED = [(CAP * W, U16), CAP, (R + 1, I64), STATUS]
+ENTRIES = {
+    "count": [TOPK, T, k, E, 1, (E, I32), STATUS],
+    "plan": [LOAD, "g", "plan", "ws"],
+    "plan_noalloc": [LOAD, "g", "plan"],
+    "plan_replicate": [LOAD, "g", "plan", "ws"],
+    "plan_reroute": [LOAD, "g", "plan"],
+    "dispatch": [(T * H, U16), TOPK, T, k, H, 1, "g", "plan", (V * H, U16), ROWS, (R * S + 1, I64),
+                 "ws", STATUS],
+    "dispatch_layout": [TOPK, T, k, 1, "g", "plan", ROWS, (R * S + 1, I64), "ws", STATUS],
+    "dispatch_scatter": [(T * H, U16), T, k, H, ROWS, (1, I64), (V * H, U16)],
+    "pack_replicas": [(E // R * W, U16), W, 1, "g", "plan"] + PACKED,
+    "reroute_and_pack": [LOAD, "g", "plan", (E // R * W, U16), W, 1] + PACKED,
+    "relay_plan": ["g", "plan", 1, (R * NS, I32), (R, I32), (4, I64), STATUS],
+    "pack_relay": [(E // R * W, U16), (NS * W, U16), W, 1, "g", "plan", (R * NS, I32)] + PACKED,
+    "combine": [(V * H, U16), V, (V, F32), ROWS, T, k, H, (T * H, U16), STATUS],
+    "grad_reduce": [(E // R * W, F32), (CAP * W, F32), W, 1, "g", "plan", CAP, STATUS],
+}
+
+
 @pytest.fixture
 def ctypes_only(monkeypatch):
     """The ctypes half alone: every native function declines."""
@@ -99,8 +124,22 @@ def test_both_halves_agree(ctypes_only, how):
 
 
 def test_native_half_takes_the_ordinary_call(monkeypatch):
-    """No call of a step reaches the ctypes code."""
+    """No call of a step reaches the ctypes code: the native half takes every
+    one of the entry points, and a refusal of the library comes through it."""
+    native, seen = uep._load_native(), set()
+
+    class Takes:
+        def __getattr__(self, name):
+            def call(*a):
+                rc = getattr(native, name)(*a)
+                assert rc is not None, name
+                seen.add(name)
+                return rc
+            return call
+    monkeypatch.setattr(uep, "_native", Takes())
     whole_step(None)
+    assert seen == set(ENTRIES)
+    monkeypatch.setattr(uep, "_native", native)
     monkeypatch.setattr(uep, "_need", None)
     monkeypatch.setattr(uep, "_ptr", None)
     st, c = gp.zero_status(), torch.zeros(E, dtype=torch.int32, device=gp.DEV)
@@ -109,6 +148,37 @@ def test_native_half_takes_the_ordinary_call(monkeypatch):
     big = torch.zeros(2000, dtype=torch.int32, device=gp.DEV)
     with pytest.raises(uep.UltraEPError):  # a refusal of the library itself (E > 1024)
         uep.ultraep_count(None, 0, 3, 2000, 1, big, st)
+
+
+@pytest.mark.parametrize("name", list(ENTRIES))
+def test_every_buffer_is_checked(name):
+    """Each buffer of each entry point on the host, strided, one element short,
+    of another element size or missing: the native half leaves the call to
+    the ctypes half (nothing is enqueued), which refuses it."""
+    g = uep.Group(R, E, NS, 1)
+    plan = uep.Plan(g, gp.DEV)
+    args = [torch.zeros(a[0], dtype=a[1], device=gp.DEV) if isinstance(a, tuple)
+            else {"g": g, "plan": plan, "ws": plan.ws}.get(a, a) for a in ENTRIES[name]]
+    native, python = getattr(uep._load_native(), name), getattr(uep, "ultraep_" + name)
+    for i, a in enumerate(ENTRIES[name]):
+        if not isinstance(args[i], torch.Tensor):
+            continue
+        t = args[i]
+        n = t.numel()
+        bad = {"host": t.cpu()}
+        if n > 1:
+            bad["strided"] = torch.zeros(2 * n, dtype=t.dtype, device=gp.DEV)[::2]
+        if a != "ws":
+            bad.update(short=t[:-1], missing=None,
+                       width=torch.zeros(n, dtype=I32 if t.dtype != I32 and t.dtype != F32 else I64,
+                                         device=gp.DEV))
+        for how, b in bad.items():
+            call = args[:i] + [b] + args[i + 1:]
+            assert native(*call, None) is None, (name, i, how)
+            with pytest.raises(ValueError):
+                python(*call)
+    for i in range(len(args)):  # and none is left out of the arguments
+        assert native(*args[:i], *args[i + 1:], None) is None
 
 
 @pytest.mark.parametrize("bad", ["host", "strided", "short", "width", "missing"])
