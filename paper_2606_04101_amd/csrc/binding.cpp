@@ -5,9 +5,9 @@
 // enqueued; the Python half then handles it and raises its errors.
 //
 // A step is five calls of up to twelve arguments; checked and marshalled in
-// Python each took 5-8 us of host time, which was most of a small step:
-// enqueueing the tiny workload's step (9 kernels) took 54-60 us, 36 us with
-// this file.
+// Python each takes 5-8 us of host time, which is most of a small step:
+// enqueueing the tiny workload's step (8 kernels) takes 53 us through the Python
+// half and 25 us through this file.
 #include <Python.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>

@@ -623,8 +623,11 @@ hipError_t launch_dispatch_layout(const int32_t *topk, int64_t V, int32_t rank,
 constexpr int kScThreads = 256;
 constexpr int kScWaves = kScThreads / kWave;
 // Resident workgroups of the streaming scatter (two per CU); each wave then
-// walks tokens t, t + 2048, ...  Measured against one wave per token and
-// against 256 to 1024 workgroups on the DeepSeek-V3-shaped layer.
+// walks tokens t, t + 2048, ...  Whole rows, 256 / 512 / 1024 workgroups over
+// rotating buffers, k = 8, us: H = 7168, 4096 tokens 102.3 / 97.5 / 102.3; H = 4096,
+// 4096 59.0 / 58.1 / 61.3; H = 2880, 2999 30.6 / 29.8 / 30.1; but narrow rows and
+// many tokens do better with more (H = 4096, 8192 123.2 / 119.9 / 116.4; H = 2880,
+// 8192 86.8 / 85.7 / 80.6; H = 256, 16384 28.3 / 21.2 / 16.0).
 constexpr int kScGrid = 512;
 constexpr int64_t kScFill = 2048;  // units that fill the resident waves
 constexpr int kScWide = 16;        // 64-chunk steps of a unit of a wide row at most

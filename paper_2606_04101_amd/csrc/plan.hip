@@ -253,11 +253,11 @@ __device__ __forceinline__ int wave_shl1(int v) {
 }
 
 // Greedy feasibility probes of SolveReplication at threshold tau (Sec. 5.1),
-// one wave each.  Lane i holds the i-th rank of the visiting order (rk_r,
-// rank, and rk_l, its load: descending load, ties to the lower rank) and
-// the i-th rank of ascending load (as_r, as_l).  A probe returns the number
-// of accepted transfers, recorded in s_re / s_rd as (e | t << 16, delta) in
-// acceptance order, or -1 if the threshold is infeasible.
+// one wave each.  Lane i holds the excess over tau of the i-th rank of the
+// visiting order (descending load, ties to the lower rank) and the i-th rank of
+// ascending load with that load.  A probe returns the number of accepted
+// transfers, recorded as (e | t << 16, delta) in acceptance order, or -1 if the
+// threshold is infeasible.
 //
 // The admissible targets (slack > 0, a free slot) form a list sorted by
 // slack descending, rank ascending, one per lane from the head h on.  It
