@@ -347,11 +347,9 @@ __global__ void __launch_bounds__(kDlThreads) k_dl_rows(DlArgs a) {
   const int32_t *h = a.ws.hist + e_t;
   const bool many = nsum > kSumFirst * parts;  // else the other loads are skipped
   const bool more = nsum > (kSumFirst + kSumSecond) * parts;
-  int hv[kSumFirst] = {}, hw[kSumBatch] = {};
-  if (part < parts) {
+  int hv[kSumFirst], hw[kSumBatch];
 #pragma unroll
-    for (int u = 0; u < kSumFirst; ++u) hv[u] = h[min(part + u * parts, nsum - 1) * E];
-  }
+  for (int u = 0; u < kSumFirst; ++u) hv[u] = h[min(part + u * parts, nsum - 1) * E];
   if (many && part < parts) {
 #pragma unroll
     for (int u = 0; u < kSumSecond; ++u)
