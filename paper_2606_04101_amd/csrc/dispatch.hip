@@ -49,7 +49,8 @@ static_assert(kLutIters * kDlThreads >= 1024 + 256 && kLutIters * kDlThreads >= 
               "the lookup tables fit the staging loops");
 constexpr int kOneChunks = 10;  // chunks up to which one launch makes the layout
 constexpr int kOneBatch = 8;    // ids of earlier chunks in flight per thread
-constexpr int kOneCopies = 8;   // counts of them at most, dealt over the lanes
+constexpr int kOneCopies = 8;   // counts of them at most, dealt over the lanes,
+constexpr int kOneFew = 2;      // for two chunks
 constexpr int kSteps = kSlotsPerWave / kWave;  // 64-slot steps per wave
 
 size_t dispatch_ws_bytes(int64_t V, int32_t E, int32_t ncol) {
@@ -518,9 +519,16 @@ __global__ void __launch_bounds__(kDlThreads) k_dl_one(DlArgs a) {
     int run = 0, w[kDlWaves];
     if (n_prev > 0) {
 #pragma unroll
-      for (int p = 0; p < kOneCopies; ++p) {
+      for (int p = 0; p < kOneFew; ++p) {
         const int v = prev[min(p, a.copies - 1) * stride + tid];
         run += p < a.copies ? v : 0;
+      }
+      if (a.copies > kOneFew) {
+#pragma unroll
+        for (int p = kOneFew; p < kOneCopies; ++p) {
+          const int v = prev[min(p, a.copies - 1) * stride + tid];
+          run += p < a.copies ? v : 0;
+        }
       }
     }
     const int before = share_before(t.q, t.hp[tid], a.ncol);
@@ -577,10 +585,14 @@ hipError_t launch_dispatch_layout(const int32_t *topk, int64_t V, int32_t rank,
   // chunks 9.0 / 8.2, 16 chunks 9.0 / 9.0; two experts alone: 4 chunks 10.0 /
   // 8.5, 10 chunks 10.1 / 10.3, 12 chunks 10.2 / 10.7; one expert alone: 8 chunks
   // 10.9 / 10.3, 10 chunks 10.8 / 11.0, 12 chunks 10.8 / 11.4.  The same line at
-  // E = 8, 256 and 512.  Where LDS does not hold all the copies of the counts, a
-  // hot expert's chunks cost more: E = 640, four copies, one expert alone: 5
-  // chunks 11.8 / 11.2, 6 chunks 11.9 / 12.0, 8 chunks 11.9 / 12.6.
-  a.copies = kOneCopies;
+  // E = 8, 256 and 512.  Two chunks do with two copies (spread ids 6.7 us against
+  // 6.8 with eight, one expert alone 9.7 against 9.2).  Where LDS holds fewer
+  // copies the line lies where one expert alone loses about half of what spread
+  // ids win, two launches / one: four copies (R = 8, E = 600), 8 chunks 9.7 / 8.3
+  // spread and 11.3 / 12.1 alone, 10 chunks 10.1 / 9.0 and 11.7 / 13.2; two (R = 64,
+  // E = 640, n_slot = 4), 5 chunks 9.9 / 7.7 and 11.8 / 12.8, 6 chunks 9.8 / 8.3 and
+  // 11.8 / 13.9; one (E = 704), 3 chunks 9.7 / 7.7 and 11.7 / 12.8.
+  a.copies = ws.n_chunks <= 2 ? kOneFew : kOneCopies;
   const auto lds_for = [&](int copies) {
     return sizeof(int32_t) * static_cast<size_t>(kDlWaves * g.E + prev_ints(copies, g.E) +
                                                  lut_ints(g.E, a.ncol));
@@ -594,7 +606,7 @@ hipError_t launch_dispatch_layout(const int32_t *topk, int64_t V, int32_t rank,
   const uintptr_t ids = reinterpret_cast<uintptr_t>(topk), out = reinterpret_cast<uintptr_t>(row_of_slot);
   const uintptr_t span = static_cast<uintptr_t>(V) * sizeof(int32_t);
   const bool apart = ids + span <= out || out + span <= ids;
-  const int64_t most = a.copies == kOneCopies ? kOneChunks : 2 + a.copies;
+  const int64_t most = a.copies == kOneCopies ? kOneChunks : a.copies == 4 ? 8 : a.copies == 2 ? 5 : 3;
   if (ws.n_chunks > 0 && ws.n_chunks <= most &&
       (apart || ws.n_chunks == 1) && lds_one <= 64 * 1024) {
     hipLaunchKernelGGL(k_dl_one, dim3(ws.n_chunks), dim3(kDlThreads), lds_one, stream, a);

@@ -253,7 +253,8 @@ def test_layout_in_place(V):
 # the one launch's counts in 8, 4, 2 and 1 copies (as many as LDS holds), up to
 # the chunks that each takes and past them, half of the ids one expert
 @pytest.mark.parametrize("R,E,NS", [(64, 512, 4), (64, 640, 1), (64, 640, 4), (64, 704, 1)])
-@pytest.mark.parametrize("V", [2 * 2048 + 65, 3 * 2048, 4 * 2048, 6 * 2048, 6 * 2048 + 1])
+@pytest.mark.parametrize("V", [2 * 2048, 2 * 2048 + 65, 3 * 2048, 4 * 2048, 5 * 2048, 5 * 2048 + 1,
+                               8 * 2048, 8 * 2048 + 1])
 def test_layout_copies_of_the_counts(R, E, NS, V):
     rng = np.random.default_rng(V + E + NS)
     tk = rng.integers(-1, E, (R, V, 1)).astype(np.int32)
