@@ -778,8 +778,9 @@ hipError_t launch_dispatch_scatter(const uint16_t *x, int64_t T, int32_t k,
   // 4.8 / 5.6), where others lose (H = 12288, k = 4, 511, 1022 units 18.5 / 12.7 / 13.5).
   const auto units = [&](int u) { return T * ((per_lane + u - 1) / u); };
   const bool wide = per_lane > kScWide;
-  const int64_t whole = k >= 12 && per_lane > 2 ? 512 : k >= 8 && per_lane > 8 ? 640 : 768;
-  if (wide && units(kScWide) >= (nch % 8 == 0 ? 2 * kScFill / 3 : k >= 4 ? 600 : 768)) {
+  const bool lines = nch % 8 == 0;
+  const int64_t whole = !lines ? 768 : k >= 12 && per_lane > 2 ? 512 : k >= 8 && per_lane > 8 ? 640 : 768;
+  if (wide && units(kScWide) >= (lines ? 2 * kScFill / 3 : k >= 4 ? 600 : 768)) {
     start(start_scatter<kScWide, true>);
   } else if (wide || (per_lane > 1 && T < whole)) {
     if (per_lane > 8 && units(8) >= kScFill * 4 / 3) start(start_scatter<8, true>);
