@@ -679,12 +679,13 @@ __device__ __forceinline__ void store_rows(const v4u (&v)[U], int rows, int k, i
 
 // Rows of up to 64 * U chunks (H <= 8192), one unit each, or (kSplit) rows cut
 // into `pieces` units of `per` <= 64 * U chunks: persistent waves, each holding
-// one unit in registers while the next one is being loaded.
+// one unit in registers while the next one is being loaded.  A wave takes `run`
+// units in a row (1, or all of a token's) before it goes on by the grid.
 template <int U, bool kSplit>
 __global__ void __launch_bounds__(kScThreads)
 k_scatter(const v4u *__restrict__ x, int64_t T, int32_t k, int32_t nch, int32_t pieces,
-          int32_t per, const int32_t *__restrict__ row_of_slot, const int64_t *n_routed,
-          v4u *__restrict__ send) {
+          int32_t per, int32_t run, const int32_t *__restrict__ row_of_slot,
+          const int64_t *n_routed, v4u *__restrict__ send) {
   constexpr bool kPlain = kSplit && U == kScWide;
   const int lane = lane_id();
   const int64_t V = T * k, n = kSplit ? T * pieces : T;
@@ -702,13 +703,18 @@ k_scatter(const v4u *__restrict__ x, int64_t T, int32_t k, int32_t nch, int32_t 
     }
     rows = lane < k ? row_of_slot[t * k + lane] : -1;
   };
-  int64_t unit = gw;
+  int64_t unit = kPlain ? gw * run : gw;
+  int left = run;
   if (unit < n) {
     v4u v[U];
     int rows, c0;
     fetch(unit, v, rows, c0);
     for (;;) {
-      const int64_t un = unit + nw;
+      int64_t un = unit + nw;
+      if constexpr (kPlain) {
+        left = left > 1 ? left - 1 : run;
+        un = unit + 1 + (left == run ? (nw - 1) * run : 0);
+      }
       v4u w[U];
       int rn = -1, cn = 0;
       if (un < n) fetch(un, w, rn, cn);
@@ -733,14 +739,15 @@ k_scatter(const v4u *__restrict__ x, int64_t T, int32_t k, int32_t nch, int32_t 
 
 template <int U, bool kSplit>
 static void start_scatter(const v4u *x, int64_t T, int32_t k, int32_t nch, const int32_t *row_of_slot,
-                          const int64_t *n_routed, v4u *send, hipStream_t stream) {
+                          const int64_t *n_routed, v4u *send, hipStream_t stream, bool together) {
   const int32_t pieces = kSplit ? (nch + U * kWave - 1) / (U * kWave) : 1;
   // the pieces of a wide row are equal, in whole 128-byte lines of an aligned row
   const int32_t per = U == kScWide ? ((nch + pieces - 1) / pieces + 7) / 8 * 8 : U * kWave;
-  const int64_t need = (T * pieces + kScWaves - 1) / kScWaves;
+  const int32_t run = together ? pieces : 1;
+  const int64_t need = (T * (pieces / run) + kScWaves - 1) / kScWaves;
   hipLaunchKernelGGL((k_scatter<U, kSplit>), dim3(static_cast<unsigned>(need < kScGrid ? need : kScGrid)),
-                     dim3(kScThreads), 0, stream, x, T, k, nch, pieces, per, row_of_slot,
-                     n_routed, send);
+                     dim3(kScThreads), 0, stream, x, T, k, nch, pieces, per, run,
+                     row_of_slot, n_routed, send);
 }
 
 hipError_t launch_dispatch_scatter(const uint16_t *x, int64_t T, int32_t k,
@@ -751,7 +758,9 @@ hipError_t launch_dispatch_scatter(const uint16_t *x, int64_t T, int32_t k,
   const int per_lane = nch / kWave + (nch % kWave != 0);
   const v4u *xs = reinterpret_cast<const v4u *>(x);
   v4u *sd = reinterpret_cast<v4u *>(send);
-  const auto start = [&](auto f) { f(xs, T, k, nch, row_of_slot, n_routed, sd, stream); };
+  const auto start = [&](auto f, bool together = false) {
+    f(xs, T, k, nch, row_of_slot, n_routed, sd, stream, together);
+  };
   // Whole rows per wave keep the stores of a row together; they are cut where
   // that leaves waves idle or where a row does not fit the registers.  Measured
   // over rotating buffers (past the last-level cache), us.
@@ -773,15 +782,19 @@ hipError_t launch_dispatch_scatter(const uint16_t *x, int64_t T, int32_t k,
   // row in passes / units of 8 steps, sc1 / these: H = 12288, 1500 tokens, k = 1
   // 17.9 / 21.1 / 15.9, k = 8 70.8 / 65.8 / 63.0; H = 9216, 1500, k = 1 14.7 / 17.1 /
   // 13.0; rows that are no whole lines, H = 8200, 4096, k = 1 31.5 / 37.4 / 31.1,
-  // k = 8 154 / 176 / 155, k = 16, 767 55.8 / 69.3 / 59.6.  Such rows change over
-  // earlier (H = 8200, k = 8, 300 tokens, 600 units 18.3 / 15.1 / 12.4 but k = 1 8.2 /
-  // 4.8 / 5.6), where others lose (H = 12288, k = 4, 511, 1022 units 18.5 / 12.7 / 13.5).
+  // k = 8 154 / 176 / 155.  Such rows change over earlier (H = 8200, k = 8, 300
+  // tokens, 600 units 18.3 / 15.1 / 12.4 but k = 1 8.2 / 4.8 / 5.6), where others
+  // lose (H = 12288, k = 4, 511, 1022 units 18.5 / 12.7 / 13.5), and with many rows one
+  // wave writes a token's pieces one after another: pieces dealt to all waves / to
+  // the token's: H = 10008, 519 tokens, k = 16 51.8 / 41.8, k = 8 23.2 / 21.8, k = 6
+  // 17.6 / 18.3; H = 12296, 1500, k = 12 134.5 / 121.1, k = 2 21.7 / 21.8, 400, k = 16
+  // 43.8 / 37.4, k = 10 24.7 / 27.2.
   const auto units = [&](int u) { return T * ((per_lane + u - 1) / u); };
   const bool wide = per_lane > kScWide;
   const bool lines = nch % 8 == 0;
   const int64_t whole = !lines ? 768 : k >= 12 && per_lane > 2 ? 512 : k >= 8 && per_lane > 8 ? 640 : 768;
   if (wide && units(kScWide) >= (lines ? 2 * kScFill / 3 : k >= 4 ? 600 : 768)) {
-    start(start_scatter<kScWide, true>);
+    start(start_scatter<kScWide, true>, !lines && T * k >= (T >= 500 ? 4000 : 6400));
   } else if (wide || (per_lane > 1 && T < whole)) {
     if (per_lane > 8 && units(8) >= kScFill * 4 / 3) start(start_scatter<8, true>);
     else if (per_lane > 4 && units(4) >= kScFill * 4 / 3) start(start_scatter<4, true>);
