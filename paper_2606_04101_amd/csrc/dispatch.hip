@@ -775,25 +775,26 @@ hipError_t launch_dispatch_scatter(const uint16_t *x, int64_t T, int32_t k,
   // empty (4 / 2 steps: H = 6144, k = 8, 683 tokens, 2049 / 4098 units 18.9 / 15.1;
   // H = 5120, k = 2, 767, 2301 / 3835 8.3 / 6.5; H = 8192, k = 8, 600, 2400 / 4800
   // 19.3 / 17.8).
-  // Wide rows take equal pieces of up to 16 steps and ordinary stores once these
-  // make two thirds of the resident waves: sc1 stores go past the L2, which
-  // otherwise joins the lines that two rows or two pieces share, and narrow rows
-  // per token write too little for sc1 to matter.  One wave per token walking the
-  // row in passes / units of 8 steps, sc1 / these: H = 12288, 1500 tokens, k = 1
-  // 17.9 / 21.1 / 15.9, k = 8 70.8 / 65.8 / 63.0; H = 9216, 1500, k = 1 14.7 / 17.1 /
-  // 13.0; rows that are no whole lines, H = 8200, 4096, k = 1 31.5 / 37.4 / 31.1,
-  // k = 8 154 / 176 / 155.  Such rows change over earlier (H = 8200, k = 8, 300
-  // tokens, 600 units 18.3 / 15.1 / 12.4 but k = 1 8.2 / 4.8 / 5.6), where others
-  // lose (H = 12288, k = 4, 511, 1022 units 18.5 / 12.7 / 13.5), and with many rows one
-  // wave writes a token's pieces one after another: pieces dealt to all waves / to
-  // the token's: H = 10008, 519 tokens, k = 16 51.8 / 41.8, k = 8 23.2 / 21.8, k = 6
-  // 17.6 / 18.3; H = 12296, 1500, k = 12 134.5 / 121.1, k = 2 21.7 / 21.8, 400, k = 16
-  // 43.8 / 37.4, k = 10 24.7 / 27.2.
+  // Wide rows that are no whole lines take equal pieces of up to 16 steps and
+  // ordinary stores from 800 units on: sc1 stores pass the L2 by, which otherwise
+  // joins the lines that two rows or two pieces share.  One wave per token walking
+  // the row in passes / units of 8 steps, sc1 / these: H = 8200, 4096 tokens, k = 1
+  // 31.5 / 37.4 / 31.1, k = 8 154 / 176 / 155; H = 12296, 519, k = 4 19.1 / 22.8 / 15.6.
+  // Below, and where all buffers stay in the last-level cache, units of up to 8
+  // steps are ahead (three states of 56 MB in turn, 355 tokens of H = 8744, k = 8,
+  // with the plan and the combine 60.6 us, these 63.3; three of 106 MB, 612 of H =
+  // 9592 27.2 and 28.6).  With many rows one wave writes a token's pieces one after
+  // another; pieces dealt to all waves / to the token's: H = 10008, 519 tokens, k =
+  // 16 51.8 / 41.8, k = 8 23.2 / 21.8, k = 6 17.6 / 18.3; H = 12296, 1500, k = 12 134.5 /
+  // 121.1, k = 2 21.7 / 21.8, 400, k = 16 43.8 / 37.4, k = 10 24.7 / 27.2.
+  // Rows of whole lines do so for one row a token only (H = 12288, 1500 tokens 17.9 /
+  // 21.1 / 15.9): with more, ordinary stores leave their write-back to the next
+  // kernel (H = 9216, 9834 tokens, k = 2 in a step 159 with sc1, 164 without).
   const auto units = [&](int u) { return T * ((per_lane + u - 1) / u); };
   const bool wide = per_lane > kScWide;
   const bool lines = nch % 8 == 0;
   const int64_t whole = !lines ? 768 : k >= 12 && per_lane > 2 ? 512 : k >= 8 && per_lane > 8 ? 640 : 768;
-  if (wide && units(kScWide) >= (lines ? 2 * kScFill / 3 : k >= 4 ? 600 : 768)) {
+  if (wide && units(kScWide) >= (lines ? (k == 1 ? 2 * kScFill / 3 : INT64_MAX) : 800)) {
     start(start_scatter<kScWide, true>, !lines && T * k >= (T >= 500 ? 4000 : 6400));
   } else if (wide || (per_lane > 1 && T < whole)) {
     if (per_lane > 8 && units(8) >= kScFill * 4 / 3) start(start_scatter<8, true>);
