@@ -764,12 +764,14 @@ hipError_t launch_dispatch_scatter(const uint16_t *x, int64_t T, int32_t k,
   // Whole rows per wave keep the stores of a row together; they are cut where
   // that leaves waves idle or where a row does not fit the registers.  Measured
   // over rotating buffers (past the last-level cache), us.
-  // Rows of up to 16 steps of 64 chunks are cut below `whole` tokens, whole / cut,
+  // Rows of up to 16 steps of 64 chunks are cut below `whole` tokens (below 768 where
+  // they are no whole lines: k = 12, H = 7240, 633 tokens 35.2 / 33.9), whole / cut,
   // k = 8: H = 4096, 511 tokens 10.4 / 8.2, 700 11.4 / 10.9; H = 5120, 600 12.4 /
   // 11.4, 700 12.8 / 15.6; H = 7168, 511 15.7 / 13.2, 640 16.5 / 17.4, 767 18.3 /
   // 19.6; k = 16: H = 4096, 511 15.1 / 14.1, 700 17.6 / 18.9; H = 5120, 600 19.4 /
-  // 20.7; H = 1024, 640 6.2 / 5.6; k = 1: H = 7168, 767 9.0 / 7.9.  More rows a
-  // token keep the memory busy with fewer waves.
+  // 20.7; H = 1024, 640 6.2 / 5.6; k = 12: H = 3712, 597 in a whole step 53.4 / 51.5;
+  // k = 1: H = 7168, 767 9.0 / 7.9.  More rows a token keep the memory busy with
+  // fewer waves.
   // The units are the widest that are enough: of 4 steps and more, a third over
   // the resident waves, as a few units over them leave the second turn nearly
   // empty (4 / 2 steps: H = 6144, k = 8, 683 tokens, 2049 / 4098 units 18.9 / 15.1;
@@ -787,13 +789,17 @@ hipError_t launch_dispatch_scatter(const uint16_t *x, int64_t T, int32_t k,
   // another; pieces dealt to all waves / to the token's: H = 10008, 519 tokens, k =
   // 16 51.8 / 41.8, k = 8 23.2 / 21.8, k = 6 17.6 / 18.3; H = 12296, 1500, k = 12 134.5 /
   // 121.1, k = 2 21.7 / 21.8, 400, k = 16 43.8 / 37.4, k = 10 24.7 / 27.2.
-  // Rows of whole lines do so for one row a token only (H = 12288, 1500 tokens 17.9 /
-  // 21.1 / 15.9): with more, ordinary stores leave their write-back to the next
-  // kernel (H = 9216, 9834 tokens, k = 2 in a step 159 with sc1, 164 without).
+  // Rows of whole lines, or halves, do so for one row a token only (H = 12288, 1500
+  // tokens 17.9 / 21.1 / 15.9): with more, ordinary stores leave their write-back to
+  // the next kernel (a whole step, H = 9216, 9834 tokens, k = 2 159 with sc1, 164
+  // without; H = 10720, 3340, k = 8 197 and 204, but H = 10952, 1557, k = 8, no whole
+  // halves, 136 and 120).
   const auto units = [&](int u) { return T * ((per_lane + u - 1) / u); };
   const bool wide = per_lane > kScWide;
-  const bool lines = nch % 8 == 0;
-  const int64_t whole = !lines ? 768 : k >= 12 && per_lane > 2 ? 512 : k >= 8 && per_lane > 8 ? 640 : 768;
+  const bool lines = nch % 4 == 0;  // rows of whole 64-byte halves of a line
+  const int64_t whole = nch % 8 || per_lane <= 2 ? 768
+                        : per_lane <= 8 ? (k >= 16 ? 512 : 768)
+                                        : (k >= 12 ? 512 : k >= 8 ? 640 : 768);
   if (wide && units(kScWide) >= (lines ? (k == 1 ? 2 * kScFill / 3 : INT64_MAX) : 800)) {
     start(start_scatter<kScWide, true>, !lines && T * k >= (T >= 500 ? 4000 : 6400));
   } else if (wide || (per_lane > 1 && T < whole)) {

@@ -154,9 +154,9 @@ def test_scatter_units(T, k, H):
 # waves, and wide rows in equal pieces with ordinary stores (whole lines or not,
 # one and several units per wave, a last piece of one chunk)
 @pytest.mark.parametrize("T,k,H", [
-    (511, 16, 1032), (512, 16, 1032), (639, 8, 4608), (640, 8, 4608), (767, 8, 4096), (683, 3, 6144),
-    (682, 3, 4104), (511, 12, 1032), (512, 12, 1032), (399, 2, 8200), (400, 2, 8200), (682, 1, 8704),
-    (683, 1, 8704), (911, 2, 8704), (1100, 1, 8200),
+    (511, 16, 1032), (639, 8, 4608), (640, 8, 4608), (767, 8, 4096), (683, 3, 6144),
+    (682, 3, 4104), (511, 16, 2048), (512, 16, 2048), (511, 12, 4608), (512, 12, 4608), (399, 2, 8200), (400, 2, 8200), (682, 1, 8704),
+    (683, 1, 8704), (911, 2, 8704), (911, 2, 8736), (1100, 1, 8200),
     (267, 3, 16392), (266, 3, 16392), (1367, 1, 24576), (499, 9, 8200), (500, 8, 8200), (503, 9, 24584),
     (400, 16, 8200), (399, 16, 8264), (4099, 1, 8200)])
 def test_scatter_lines(T, k, H):
